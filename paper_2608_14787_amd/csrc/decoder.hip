@@ -69,8 +69,6 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmArgs a) {
   constexpr int R = TB * 16;       // padded rows of this pass
   constexpr int NACC = NG * TB;    // 16x16 accumulator tiles per wave
   constexpr int IPW = (NACC + 3) / 4;
-  constexpr int EPL = 16 / sizeof(T);
-  constexpr int KTILE = 4 * EPL;
   constexpr int EPT4 = (R * C / 4 + kGemmThreads - 1) / kGemmThreads;  // tile float4s per thread (cross-workgroup reduction)
   // each wave's accumulators; after the cross-wave sum the same memory holds the output tile [R][CP]
   __shared__ f32x4 red[4][NACC][kWave];
@@ -89,23 +87,22 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmArgs a) {
   const int g_first = (int)(u0 / KT);
   const uint4* W = reinterpret_cast<const uint4*>(a.W);
   const int MC = a.M * C;
-  // activation fragments by buffer loads: descriptor in scalars, the lane's byte offset in one 32-bit register,
-  // the k-step as a scalar offset, so that no address registers are recomputed in the stream (a recomputed
-  // address register can alias an in-flight load's destination and force a full wait)
-  // The descriptor's range ends at the pass's last row: fragments of the padded rows (33 rows pad to 48) are
-  // out of range, read as zero without a memory access (a row's offset is at least row x ldx elements and
-  // below (row + 1) x ldx, so every real row is in range and every padded one is not)
+  // activation fragments by buffer loads: descriptor in scalars, the lane's byte offset in one 32-bit register
+  // per row tile, the k-step as a scalar offset, so that no address registers are recomputed in the stream (a
+  // recomputed address register can alias an in-flight load's destination and force a full wait).  A fragment
+  // is one contiguous KiB; the lanes of padded rows (33 rows pad to 48) cost no traffic (xfrag_lane).
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<char*>(a.X), 0, (a.m0 + a.M) * a.ldx * (int)sizeof(T), kBufferRsrcWord3);
-  const int xlane = ((a.m0 + lane % 16) * a.ldx + (lane / 16) * EPL) * (int)sizeof(T);  // < 2^31: checked on the host
-  const int xrow16 = 16 * a.ldx * (int)sizeof(T);
+      const_cast<char*>(a.X), 0, xfrag_bytes(a.m0 + a.M, a.KT), kBufferRsrcWord3);
+  int xlane[TB];  // < 2^31: checked on the host
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) xlane[tb] = xfrag_lane(a.m0 / 16 + tb, a.KT, a.m0 + a.M, lane);
   // the whole matrix, stored in the order of this launch's plan: the i-th unit (NG tiles) of workgroup w at
   // slot i * n_wg + w, so a workgroup's consecutive units are n_wg slots apart
   const uint32_t slot_bytes = (uint32_t)NG * kWave * 16, wstride = (uint32_t)a.n_wg * slot_bytes;
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint4*>(W), 0, (int)(a.share * wstride), kBufferRsrcWord3);
   const uint32_t kstep4w = 4u * wstride;    // bytes between a wave's consecutive k-steps
-  const uint32_t kstep4x = 4u * KTILE * (uint32_t)sizeof(T);
+  constexpr uint32_t kstep4x = 4u * 1024;
   const int wlane = lane * 16;
 
   // a descriptor with no range: every load through it returns zero without a memory access
@@ -129,7 +126,7 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmArgs a) {
                                              wd, wlane, (int)(wo + (uint32_t)kt * kstep4w + (uint32_t)nt * kWave * 16), kNtCpol));
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb)
-      xb[tb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xd, xlane + tb * xrow16,
+      xb[tb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xd, xlane[tb],
                                                                                  (int)(xo + (uint32_t)kt * kstep4x), 0));
     // keep the next stages' loads ahead of this stage's MFMAs
     __builtin_amdgcn_sched_barrier(0);
@@ -138,8 +135,8 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmArgs a) {
   // wave w streams k-tiles kb + w, kb + w + 4, ... (kz of them), so that at any
   // time the four waves read adjacent k-steps and, the matrix being stored
   // k-step by k-step, the launch reads few long runs of memory.  wo and xo are
-  // the byte offsets of the wave's first k-step in the weights and in an
-  // activation row.
+  // the byte offsets of the wave's first k-step in the weights and in a row
+  // tile of the activations.
   struct Seg {
     int g, kb, ke, ka, kz;
     uint32_t wo, xo;
@@ -154,7 +151,7 @@ __global__ void __launch_bounds__(kGemmThreads, 1) gemm_kernel(GemmArgs a) {
     s.kz = __builtin_amdgcn_readfirstlane(S > wave ? (S - wave + 3) / 4 : 0);
     const uint32_t k0 = (uint32_t)(s.kb + wave);
     s.wo = __builtin_amdgcn_readfirstlane((u - u0 + (uint32_t)wave) * wstride + (uint32_t)w * slot_bytes);
-    s.xo = __builtin_amdgcn_readfirstlane(k0 * KTILE * (uint32_t)sizeof(T));
+    s.xo = __builtin_amdgcn_readfirstlane(k0 * 1024u);
     return s;
   };
   // Row info and RMSNorm row scales of this pass, used only by the epilogues.
@@ -445,7 +442,7 @@ __device__ inline void ws_epilogue_swiglu(const GemmArgs& a, const f32x4* v, int
       const float up = v[2 * t + 1][e] * r;
       hv[e] = gt / (1.f + expf(-gt)) * up;
     }
-    const int64_t off = (int64_t)(a.m0 + mm) * a.dff + (int64_t)g * 64 + t * 16 + 4 * (lane / 16);
+    const int64_t off = xfrag_index<uint16_t>(a.m0 + mm, g * 64 + t * 16 + 4 * (lane / 16), a.dff / 32);
     *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.ffh) + off) =
         make_uint2(pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3]));
   }
@@ -501,7 +498,7 @@ template <int TB, int EPI>
 __global__ void __launch_bounds__(kWsThreads, 1) gemm_ws_kernel(GemmArgs a) {
   static_assert(EPI == EPI_SWIGLU || EPI == EPI_LOGITS, "register-only epilogues");
   static_assert(TB >= 1 && TB <= 3, "at most 48 rows");
-  constexpr int NG = 8, C = NG * 16, NACC = NG * TB, EPL = 8, KTILE = 32;
+  constexpr int NG = 8, C = NG * 16, NACC = NG * TB;
   __shared__ f32x4 red[4][NACC][kWave];
   __shared__ int s_fill, s_free;
   touch_kernargs<GemmArgs>();
@@ -519,14 +516,15 @@ __global__ void __launch_bounds__(kWsThreads, 1) gemm_ws_kernel(GemmArgs a) {
     // ---- streaming waves ----
     const int wave = wv;
     const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(a.X), 0, (a.m0 + a.M) * a.ldx * 2, kBufferRsrcWord3);
-    const int xlane = ((a.m0 + lane % 16) * a.ldx + (lane / 16) * EPL) * 2;  // < 2^31: checked on the host
-    const int xrow16 = 16 * a.ldx * 2;
+        const_cast<char*>(a.X), 0, xfrag_bytes(a.m0 + a.M, a.KT), kBufferRsrcWord3);
+    int xlane[TB];  // < 2^31: checked on the host
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) xlane[tb] = xfrag_lane(a.m0 / 16 + tb, a.KT, a.m0 + a.M, lane);
     const uint32_t slot_bytes = (uint32_t)NG * kWave * 16, wstride = (uint32_t)a.n_wg * slot_bytes;
     const __amdgpu_buffer_rsrc_t wrs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(a.W), 0, (int)(a.share * wstride), kBufferRsrcWord3);
     const __amdgpu_buffer_rsrc_t nrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(a.W), 0, 0, kBufferRsrcWord3);
-    const uint32_t kstep4w = 4u * wstride, kstep4x = 4u * KTILE * 2;
+    const uint32_t kstep4w = 4u * wstride, kstep4x = 4u * 1024;
     const int wlane = lane * 16;
     // local k-step kt of this wave in its segment (as in the 4-wave kernel)
     auto load = [&](uint32_t wo, uint32_t xo, int kt, int kz, uint4* wa, uint4* xb) {
@@ -538,7 +536,7 @@ __global__ void __launch_bounds__(kWsThreads, 1) gemm_ws_kernel(GemmArgs a) {
                                                wd, wlane, (int)(wo + (uint32_t)kt * kstep4w + (uint32_t)nt * kWave * 16), kNtCpol));
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb)
-        xb[tb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xd, xlane + tb * xrow16,
+        xb[tb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xd, xlane[tb],
                                                                                    (int)(xo + (uint32_t)kt * kstep4x), 0));
       __builtin_amdgcn_sched_barrier(0);
     };
@@ -554,7 +552,7 @@ __global__ void __launch_bounds__(kWsThreads, 1) gemm_ws_kernel(GemmArgs a) {
       s.len = (uint32_t)S;
       s.kz = __builtin_amdgcn_readfirstlane(S > wave ? (S - wave + 3) / 4 : 0);
       s.wo = __builtin_amdgcn_readfirstlane((u - u0 + (uint32_t)wave) * wstride + (uint32_t)w * slot_bytes);
-      s.xo = __builtin_amdgcn_readfirstlane((uint32_t)(kb + wave) * KTILE * 2);
+      s.xo = __builtin_amdgcn_readfirstlane((uint32_t)(kb + wave) * 1024u);
       return s;
     };
     uint4 wa0[NG], wa1[NG], wa2[NG], xb0[TB], xb1[TB], xb2[TB];
@@ -728,7 +726,7 @@ struct AttnArgs {
   const char* q;  // [rows][hq][hd]
   const char* kc;
   const char* vc;
-  char* out;      // [rows][hq*hd]
+  char* out;      // rows of hq*hd columns, fragment-major
   const RowInfo* rows;
   int m0, hq, hkv, hd, ld;  // ld: position stride of the caches
   float scale;
@@ -744,9 +742,12 @@ __global__ void __launch_bounds__(256) attention_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const RowInfo ri = a.rows[m];
   const int hd = a.hd;
-  T* outp = reinterpret_cast<T*>(a.out) + ((int64_t)m * a.hq + h) * hd;
+  // fragment-major output rows of hq * hd columns (the o_proj's input)
+  auto put = [&](int d, float v) {
+    store_t<T>(a.out, xfrag_index<T>(m, h * hd + d, a.hq * hd / (64 / (int)sizeof(T))), v);
+  };
   if (!ri.valid) {
-    for (int d = tid; d < hd; d += 256) outp[d] = Elem<T>::from_f32(0.f);
+    for (int d = tid; d < hd; d += 256) put(d, 0.f);
     return;
   }
   const int kh = h / (a.hq / a.hkv);
@@ -800,7 +801,7 @@ __global__ void __launch_bounds__(256) attention_kernel(AttnArgs a) {
   if (tid < hd) {
     float o = 0.f;
     for (int s = 0; s < nsub; ++s) o += acc2[s * hd + tid];
-    outp[tid] = Elem<T>::from_f32(o / run_l);
+    put(tid, o / run_l);
   }
 }
 
@@ -824,7 +825,7 @@ struct AttnMfmaArgs {
   const uint16_t* q;   // [rows][hq][HD]
   const uint16_t* kc;  // layer base, per (seq, hkv) ld x HD elements, fragment-major
   const uint16_t* vc;  // layer base, per (seq, hkv) ld x HD elements, fragment-major
-  uint16_t* out;       // [rows][hq*HD]
+  uint16_t* out;       // rows of hq*HD columns, fragment-major
   const RowInfo* rows;
   int nb, R, hq, hkv, grp, ld, qblocks;  // ld: position stride of the caches (multiple of 64)
   float scale;
@@ -839,7 +840,7 @@ struct AttnMfmaArgs {
 template <int HD>
 __global__ void __launch_bounds__(kAttnWaves * 64) attention_mfma_kernel(AttnMfmaArgs a) {
   constexpr int KK = HD / 32, DB = HD / 16;
-  __shared__ float s_o[kAttnWaves][16][HD + 1];
+  __shared__ __align__(16) float s_o[kAttnWaves][16][HD + 4];  // rows 4 words apart mod 64: 16-byte writes on distinct banks
   __shared__ float s_m[kAttnWaves][16], s_l[kAttnWaves][16], s_f[kAttnWaves][16], s_L[16];
   touch_kernargs<AttnMfmaArgs>();
   if ((int)blockIdx.x >= a.n_attn) {
@@ -1016,9 +1017,7 @@ __global__ void __launch_bounds__(kAttnWaves * 64) attention_mfma_kernel(AttnMfm
   ltot = xor32_op(ltot, [](float x, float y) { return x + y; });
   // publish the wave's partial to LDS: o[db][i] is O^T[16 db + 4 (lane / 16) + i][query lane%16]
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s_o[wave][lane % 16][16 * db + 4 * (lane / 16) + i] = o[db][i];
+  for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(&s_o[wave][lane % 16][16 * db + 4 * (lane / 16)]) = o[db];
   if (lane < 16) {
     s_m[wave][lane] = mrun;
     s_l[wave][lane] = ltot;
@@ -1042,16 +1041,26 @@ __global__ void __launch_bounds__(kAttnWaves * 64) attention_mfma_kernel(AttnMfm
     s_L[q] = L;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < 16 * HD; e += kAttnWaves * 64) {
-    const int q = e / HD, dim = e % HD;
+  // four consecutive dimensions per thread (one 8-byte store into the fragment-major rows)
+  for (int e = threadIdx.x; e < 16 * HD / 4; e += kAttnWaves * 64) {
+    const int q = e / (HD / 4), dim = 4 * (e % (HD / 4));
     const int qq = qb * 16 + q;
     if (qq >= QV) continue;
-    float O = 0.f;
+    f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) O += s_o[w][q][dim] * s_f[w][q];
+    for (int w = 0; w < kAttnWaves; ++w) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[w][q][dim]);
+      const float f = s_f[w][q];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) O[i] += v[i] * f;
+    }
     const float L = s_L[q];
     const int rr = qq / a.grp, hq2 = kvh * a.grp + qq % a.grp;
-    a.out[((int64_t)(blk * a.R + rr) * a.hq + hq2) * HD + dim] = f32_to_bf16(L > 0.f ? O / L : 0.f);
+    float y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = L > 0.f ? O[i] / L : 0.f;
+    *reinterpret_cast<uint2*>(a.out + xfrag_index<uint16_t>(blk * a.R + rr, hq2 * HD + dim, a.hq * HD / 32)) =
+        make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
   }
 }
 
@@ -1123,7 +1132,6 @@ __global__ void __launch_bounds__(256) embed_kernel(EmbedArgs a) {
   constexpr int EPL = 16 / sizeof(T), kRound = 4;
   const T* e = reinterpret_cast<const T*>(a.E) + (int64_t)s_tok * a.d;
   float* xrow = a.x + (int64_t)m * a.d;
-  T* xarow = reinterpret_cast<T*>(a.xa) + (int64_t)m * a.d;
   const int nv = a.d / EPL;
   float ss = 0.f;
   for (int base = 0; base < nv; base += 256 * kRound) {
@@ -1154,7 +1162,8 @@ __global__ void __launch_bounds__(256) embed_kernel(EmbedArgs a) {
           }
           *reinterpret_cast<f32x4*>(xrow + iv * EPL + 4 * q) = xo;
         }
-        *reinterpret_cast<uint4*>(xarow + iv * EPL) = *reinterpret_cast<const uint4*>(xa_out);
+        *reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.xa) + xfrag_index<T>(m, iv * EPL, a.d / (4 * EPL))) =
+            *reinterpret_cast<const uint4*>(xa_out);
       }
     }
   }
@@ -1323,7 +1332,6 @@ static int run_gemm(CallCtx& cx, int epi, unsigned prof, size_t w_off, int64_t N
   a.G = plan.G;
   a.N = (int)N;
   a.X = X;
-  a.ldx = K;
   a.mp = cx.L.mp;
   a.part = reinterpret_cast<float*>(cx.ws + cx.L.part);
   a.err = cx.kv ? cx.kv->err : nullptr;

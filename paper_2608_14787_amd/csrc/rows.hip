@@ -116,18 +116,17 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_rows_kernel(GemmArgs a) 
       const_cast<char*>(a.W), 0, (int)(a.share * kstep_w), kBufferRsrcWord3);
   // a descriptor with no range: loads through it return zero without a memory access
   const __amdgpu_buffer_rsrc_t nrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(a.W), 0, 0, kBufferRsrcWord3);
-  // activations: row r of the launch at X + (m0 + r) * ldx elements.  Row tile tb's fragment of k-step kt: lane l
-  // reads row 16 tb + l % 16, elements 32 kt + 8 (l / 16) .. + 7.  The descriptor ends at the launch's last row,
-  // so the rows of a padded tile read zero without a memory access.
+  // activations, fragment-major: row tile tb's fragment of a k-step is one contiguous KiB; the padded rows'
+  // lanes cost no traffic (xfrag_lane)
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<char*>(a.X), 0, (a.m0 + a.M) * a.ldx * (int)sizeof(T), kBufferRsrcWord3);
+      const_cast<char*>(a.X), 0, xfrag_bytes(a.m0 + a.M, a.KT), kBufferRsrcWord3);
   int xl[TBW];  // mover: byte offset of this lane's fragment of row tile wave + 4 j (< 2^31: checked on the host)
 #pragma unroll
-  for (int j = 0; j < TBW; ++j) xl[j] = ((a.m0 + 16 * (wave + 4 * j) + lane % 16) * a.ldx + (lane / 16) * 8) * 2;
+  for (int j = 0; j < TBW; ++j) xl[j] = xfrag_lane(a.m0 / 16 + wave + 4 * j, a.KT, a.m0 + a.M, lane);
 
   struct Seg {
     int g, kb, ke, nk;
-    uint32_t wo, xo;  // bytes of the segment's first k-step in the weights and in an activation row
+    uint32_t wo, xo;  // bytes of the segment's first k-step in the weights and in a row tile of the activations
   };
   auto make_seg = [&](uint32_t u) {
     Seg s;
@@ -136,7 +135,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_rows_kernel(GemmArgs a) 
     s.ke = (int)std::min<uint32_t>(KT, s.kb + (u1 - u));
     s.nk = s.ke - s.kb;
     s.wo = (u - u0) * kstep_w + (uint32_t)w * NG * 1024;
-    s.xo = (uint32_t)s.kb * 64;
+    s.xo = (uint32_t)s.kb * 1024;
     return s;
   };
   // mover: this wave's DW loads of local k-step kt into ring slot kt % RS -- weight tiles wave * NG/4 + i and
@@ -153,7 +152,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_rows_kernel(GemmArgs a) 
     }
 #pragma unroll
     for (int j = 0; j < TBW; ++j)
-      load_lds16<0>(xd, slot + (NG + wave + 4 * j) * 1024, xl[j], (int)(s.xo + (uint32_t)kt * 64));
+      load_lds16<0>(xd, slot + (NG + wave + 4 * j) * 1024, xl[j], (int)(s.xo + (uint32_t)kt * 1024));
   };
   // Row info and RMSNorm row scales of the launch's rows, for the epilogues.  A row's scale sums the producer's
   // per-group sums of squares in the 33-row kernel's order (four threads per row, every fourth group in group
@@ -398,7 +397,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_pair_kernel(GemmArgs a) 
       const_cast<char*>(a.W), 0, (int)((uint32_t)a.share * NW * NG * 1024), kBufferRsrcWord3);
   const __amdgpu_buffer_rsrc_t nrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(a.W), 0, 0, kBufferRsrcWord3);
   const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<char*>(a.X), 0, (a.m0 + a.M) * a.ldx * (int)sizeof(T), kBufferRsrcWord3);
+      const_cast<char*>(a.X), 0, xfrag_bytes(a.m0 + a.M, a.KT), kBufferRsrcWord3);
   // byte offset of this lane's fragment of each row tile the wave loads (< 2^31: checked on the host): one
   // ring, row tiles v + 8 j; two rings, row tiles wave + 4 j
   constexpr int NXL = kTwo ? TBW : XQ + 1;
@@ -406,7 +405,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_pair_kernel(GemmArgs a) 
 #pragma unroll
   for (int j = 0; j < NXL; ++j) {
     const int rt = kTwo ? wave + 4 * j : v + 8 * j;
-    xl[j] = ((a.m0 + 16 * rt + lane % 16) * a.ldx + (lane / 16) * 8) * 2;
+    xl[j] = xfrag_lane(a.m0 / 16 + rt, a.KT, a.m0 + a.M, lane);
   }
 
   // Where the storage plan keeps k-step k of column group g: unit g KT + k of owner o at slot
@@ -427,7 +426,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_pair_kernel(GemmArgs a) 
 
   struct Seg {
     int p, kb, ke, nk;
-    uint32_t xo;  // bytes of the segment's first k-step in an activation row
+    uint32_t xo;  // bytes of the segment's first k-step in a row tile of the activations
   };
   auto make_seg = [&](uint32_t u) {
     Seg s;
@@ -435,7 +434,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_pair_kernel(GemmArgs a) 
     s.kb = (int)(u - (uint32_t)s.p * KT);
     s.ke = (int)std::min<uint32_t>(KT, s.kb + (u1 - u));
     s.nk = s.ke - s.kb;
-    s.xo = (uint32_t)s.kb * 64;
+    s.xo = (uint32_t)s.kb * 1024;
     return s;
   };
   // this wave's loads of local k-step kt (one ring: weight tile v of both groups and its fragments; two
@@ -461,7 +460,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_pair_kernel(GemmArgs a) 
       const __amdgpu_buffer_rsrc_t xd = in ? xrs : nrs;
 #pragma unroll
       for (int j = 0; j <= XQ; ++j)
-        if (j < XQ || xhi) load_lds16<0>(xd, slot + (2 * NG + v + 8 * j) * 1024, xl[j], (int)(s.xo + (uint32_t)kt * 64));
+        if (j < XQ || xhi) load_lds16<0>(xd, slot + (2 * NG + v + 8 * j) * 1024, xl[j], (int)(s.xo + (uint32_t)kt * 1024));
     } else if (wload) {
       char* slot = s_big + (kt % RW) * kWS;
       const int h = v >> 1, q = 4 * (v & 1);
@@ -479,7 +478,7 @@ __global__ void __launch_bounds__(kRowsThreads, 1) gemm_pair_kernel(GemmArgs a) 
       char* slot = s_big + kXOff + (kt % RX) * kXS;
       const __amdgpu_buffer_rsrc_t xd = in ? xrs : nrs;
 #pragma unroll
-      for (int j = 0; j < TBW; ++j) load_lds16<0>(xd, slot + (wave + 4 * j) * 1024, xl[j], (int)(s.xo + (uint32_t)kt * 64));
+      for (int j = 0; j < TBW; ++j) load_lds16<0>(xd, slot + (wave + 4 * j) * 1024, xl[j], (int)(s.xo + (uint32_t)kt * 1024));
     }
   };
   // Row info and RMSNorm row scales, as in gemm_rows_kernel (the 33-row kernel's summation order).
