@@ -164,7 +164,8 @@ int sdd_workspace_init(void* ws, size_t bytes, sdd_stream_t stream);
 
 /* Prefill of sequence seq with tokens[0..n) (device int32): caches positions
  * 0..n-2, sets len = n-1 and pending = tokens[n-1].  The prompt is processed
- * in row chunks of at most max_rows of the workspace.
+ * in equal row chunks, as few and as large as the workspace's bytes hold (at
+ * most 4096 rows; fp32 models: at most 256 and max_rows).
  * The verifier KV cache is this library's reading of the verify call: the
  * paper's own verifier keeps no cache and recomputes the whole sequence every
  * call (Appendix "Evaluation and Throughput"; sdd_verify_full is that mode).

@@ -1238,7 +1238,13 @@ static size_t counters_bytes(const sdd_model* m) {
   return align_up((size_t)gemm_counter_count(m) * 4 * kCntStride, 256);
 }
 
-WsLayout ws_layout(const sdd_model* m, int max_rows) {
+// Room for one workgroup's partial tile of a split many-row GEMM (320 rows x 256 columns fp32), twice: a launch may
+// hold two rounds of them.
+constexpr size_t kTilePartBytes = (size_t)2 * 320 * 256 * 4;
+constexpr int kPrefillMaxRows = 4096;  // rows per prefill chunk at most
+
+// Everything but the partial tiles and the argmax records; total is the end so far.
+static WsLayout rows_layout(const sdd_model* m, int max_rows) {
   WsLayout L{};
   const sdd_model_config& c = m->cfg;
   const int es = m->es;
@@ -1261,13 +1267,29 @@ WsLayout ws_layout(const sdd_model* m, int max_rows) {
   L.q = take((size_t)mp * hq * es);
   L.ao = take((size_t)mp * hq * es);
   L.ffh = take((size_t)mp * c.d_ff * es);
-  // stream-K partial tiles: [n_wg][2][64 rows][128] for the 33-row kernel; the many-row kernel (bf16, more
-  // than 64 rows) keeps its partials in the accumulator layout, kRowsPartBytes per workgroup
-  size_t part = (size_t)L.n_wg * 2 * kMaxPassRows * 128 * 4;
-  if (es == 2 && max_rows > kMaxPassRows) part = std::max(part, (size_t)L.n_wg * kRowsPartBytes);
-  L.part = take(part);
-  L.amax = take((size_t)L.max_groups * mp * 8);
   L.total = off;
+  return L;
+}
+
+// stream-K partial tiles of the 33-row kernels: [n_wg][2][64 rows][128]
+static size_t part_min_bytes(const WsLayout& L) { return (size_t)L.n_wg * 2 * kMaxPassRows * 128 * 4; }
+
+WsLayout ws_layout(const sdd_model* m, int max_rows) {
+  WsLayout L = rows_layout(m, max_rows);
+  L.part_bytes = part_min_bytes(L);
+  // the many-row kernel (bf16, more than 64 rows) gets room for every workgroup's tile of a split launch
+  if (m->es == 2 && max_rows > kMaxPassRows) L.part_bytes = std::max(L.part_bytes, (size_t)L.n_wg * kTilePartBytes);
+  L.part = L.total;
+  L.amax = align_up(L.part + L.part_bytes, 256);
+  L.total = align_up(L.amax + (size_t)L.max_groups * L.mp * 8, 256);
+  return L;
+}
+
+WsLayout prefill_layout(const sdd_model* m, int rows, size_t bytes) {
+  WsLayout L = rows_layout(m, rows);
+  L.part = L.total;
+  L.part_bytes = std::max(part_min_bytes(L), bytes > L.part ? bytes - L.part : 0);
+  L.total = L.part + L.part_bytes;
   return L;
 }
 
@@ -1321,10 +1343,15 @@ static MatPlan plan_gemm(const CallCtx& cx, const GemmRef& r) {
   return plan_matrix(r.N, r.K, cx.m->ktile, r.ng, cx.L.n_wg);
 }
 
-// Runs one GEMM over rows [0, M) in passes of at most 64 rows; `next` is the
+// Whether a GEMM over M rows runs on the many-row kernel.
+static bool many_rows(const sdd_model* m, int M, int ng) {
+  return m->es == 2 && M > kMaxPassRows && (ng == 8 || ng == 4);
+}
+
+// Runs one GEMM over rows [0, M): the many-row kernel by `tp`, or passes of at most 64 rows; `next` is the
 // forward's following GEMM, whose first k-steps the last pass loads into L2.
 static int run_gemm(CallCtx& cx, int epi, unsigned prof, size_t w_off, int64_t N, int K, const char* X, GemmArgs a,
-                    int M, int ng, const GemmRef* next = nullptr) {
+                    int M, int ng, const TilePlan& tp, const GemmRef* next = nullptr) {
   const sdd_model* m = cx.m;
   const MatPlan plan = plan_gemm(cx, GemmRef{w_off, N, K, ng});
   a.W = m->base + w_off;
@@ -1353,21 +1380,14 @@ static int run_gemm(CallCtx& cx, int epi, unsigned prof, size_t w_off, int64_t N
     return fail(SDD_EUNSUPPORTED, "matrix of %lld x %d exceeds the 32-bit buffer offsets", (long long)N, K);
   if ((int64_t)(M + 64) * K * m->es >= (int64_t(1) << 31))
     return fail(SDD_EUNSUPPORTED, "activations of %d rows x %d exceed the 32-bit buffer offsets", M, K);
-  if (m->es == 2 && M > kMaxPassRows && (ng == 8 || ng == 4)) {
-    // bf16 over more than 64 rows (several sequences' blocks, prefill chunks): the many-row kernel streams
-    // the weights once per kRowsMaxRows rows, on the same stream-K partition
-    if ((int64_t)(M + kRowsMaxRows) * K * 2 >= (int64_t(1) << 31))
-      return fail(SDD_EUNSUPPORTED, "activations of %d rows x %d exceed the 32-bit buffer offsets", M, K);
+  if (many_rows(m, M, ng)) {
     a.Wn = nullptr;
-    for (int m0 = 0; m0 < M; m0 += kRowsMaxRows) {
-      a.m0 = m0;
-      a.M = std::min(kRowsMaxRows, M - m0);
-      prof_begin(prof, cx.st);
-      int rc = launch_gemm_rows(ng, epi, a, nblocks, cx.st);
-      prof_end(prof, cx.st);
-      if (rc) return rc;
-    }
-    return SDD_OK;
+    a.M = M;
+    a.ng = ng;
+    prof_begin(prof, cx.st);
+    const int rc = launch_gemm_tiles(tp, epi, a, cx.st);
+    prof_end(prof, cx.st);
+    return rc;
   }
   for (int m0 = 0; m0 < M; m0 += kMaxPassRows) {
     a.m0 = m0;
@@ -1412,6 +1432,22 @@ static int run_gemm(CallCtx& cx, int epi, unsigned prof, size_t w_off, int64_t N
   return SDD_OK;
 }
 
+// Many-row plans of a forward's GEMMs (unset where the GEMM does not take that kernel).
+struct ForwardPlans {
+  TilePlan qkv{}, o{}, gu{}, down{}, lm{};
+  double layer_us() const { return qkv.us + o.us + gu.us + down.us; }
+};
+static ForwardPlans plan_forward(const sdd_model* m, int M, size_t part_bytes, bool lm) {
+  ForwardPlans p;
+  auto plan = [&](const MatPlan& mp) { return many_rows(m, M, mp.ng) ? plan_tiles(mp, M, m->n_cu, part_bytes, gemm_counter_count(m)) : TilePlan{}; };
+  p.qkv = plan(m->plan_qkv);
+  p.o = plan(m->plan_o);
+  p.gu = plan(m->plan_gu);
+  p.down = plan(m->plan_down);
+  if (lm) p.lm = plan(m->plan_lm);
+  return p;
+}
+
 // Forward of M rows whose RowInfo/x/xa/sum of squares were written by embed_kernel.
 static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argmax) {
   const int M = nb * R;
@@ -1425,6 +1461,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
   char* xa = ws + L.xa;
   float* ss = reinterpret_cast<float*>(ws + L.ss_part);
   // column groups of the RMSNorm statistic of the current residual stream
+  const ForwardPlans tp = plan_forward(m, M, L.part_bytes, logits != nullptr);
   const int g_resid_o = (int)(d / 16 / m->ng_o), g_resid_down = (int)(d / 16 / m->ng_down);
   int ss_groups = 1;  // from embed_kernel
   int rc;
@@ -1448,7 +1485,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
       a.kc = kv->k + (size_t)l * kv->layer_stride;
       a.vc = kv->v + (size_t)l * kv->layer_stride;
       const GemmRef nx{Ly.o, d, (int)hq, m->ng_o};
-      if ((rc = run_gemm(cx, EPI_QKV, PROF_GEMM_QKV, Ly.qkv, hq + 2 * hk, (int)d, xa, a, M, m->ng_qkv, &nx))) return rc;
+      if ((rc = run_gemm(cx, EPI_QKV, PROF_GEMM_QKV, Ly.qkv, hq + 2 * hk, (int)d, xa, a, M, m->ng_qkv, tp.qkv, &nx))) return rc;
     }
     // attention
     if (m->es == 2) {
@@ -1512,7 +1549,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
       a.g_next = reinterpret_cast<const float*>(m->base + Ly.ffn_norm);
       a.ss_part = ss;
       const GemmRef nx{Ly.gu, 2 * (int64_t)c.d_ff, (int)d, m->ng_gu};
-      if ((rc = run_gemm(cx, EPI_RESID, PROF_GEMM_O, Ly.o, d, (int)hq, ws + L.ao, a, M, m->ng_o, &nx))) return rc;
+      if ((rc = run_gemm(cx, EPI_RESID, PROF_GEMM_O, Ly.o, d, (int)hq, ws + L.ao, a, M, m->ng_o, tp.o, &nx))) return rc;
     }
     // gate/up + SwiGLU
     {
@@ -1523,7 +1560,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
       a.ffh = ws + L.ffh;
       a.dff = c.d_ff;
       const GemmRef nx{Ly.down, d, c.d_ff, m->ng_down};
-      if ((rc = run_gemm(cx, EPI_SWIGLU, PROF_GEMM_GU, Ly.gu, 2 * (int64_t)c.d_ff, (int)d, xa, a, M, m->ng_gu, &nx)))
+      if ((rc = run_gemm(cx, EPI_SWIGLU, PROF_GEMM_GU, Ly.gu, 2 * (int64_t)c.d_ff, (int)d, xa, a, M, m->ng_gu, tp.gu, &nx)))
         return rc;
     }
     // down projection + residual; next input scaled by the next norm gain
@@ -1539,7 +1576,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
       const GemmRef nq{l + 1 < c.n_layers ? m->layers[l + 1].qkv : 0, hq + 2 * hk, (int)d, m->ng_qkv};
       const GemmRef nl{m->off_lm, c.vocab, (int)d, m->ng_lm};
       const GemmRef* nx = l + 1 < c.n_layers ? &nq : logits ? &nl : nullptr;
-      if ((rc = run_gemm(cx, EPI_RESID, PROF_GEMM_DOWN, Ly.down, d, c.d_ff, ws + L.ffh, a, M, m->ng_down, nx))) return rc;
+      if ((rc = run_gemm(cx, EPI_RESID, PROF_GEMM_DOWN, Ly.down, d, c.d_ff, ws + L.ffh, a, M, m->ng_down, tp.down, nx))) return rc;
       ss_groups = g_resid_down;
     }
   }
@@ -1552,7 +1589,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
     a.V = c.vocab;
     a.amax_v = reinterpret_cast<float*>(ws + L.amax);
     a.amax_i = reinterpret_cast<int*>(ws + L.amax + (size_t)L.max_groups * L.mp * 4);
-    if ((rc = run_gemm(cx, EPI_LOGITS, PROF_GEMM_LM, m->off_lm, c.vocab, (int)d, xa, a, M, m->ng_lm))) return rc;
+    if ((rc = run_gemm(cx, EPI_LOGITS, PROF_GEMM_LM, m->off_lm, c.vocab, (int)d, xa, a, M, m->ng_lm, tp.lm))) return rc;
     if (argmax) {
       const int G = (int)(c.vocab / 16 / m->ng_lm);
       prof_begin(PROF_GEMM_LM, cx.st);
@@ -1686,6 +1723,38 @@ static int make_ctx(CallCtx& cx, sdd_model* m, sdd_kv* kv, void* ws, size_t ws_b
   return SDD_OK;
 }
 
+// Rows per prefill chunk of n rows in a workspace of `bytes`.  fp32 models: the largest power of two up to 256
+// whose verify layout fits.  bf16: larger chunks amortise the weights and fill the matrix cores, so the prompt is cut
+// into equal chunks, as few as the workspace holds (without argmax records, everything past the rows' buffers
+// being room for partial tiles), or up to three more where the GEMMs' estimated time comes out lower.
+static int prefill_chunk(const sdd_model* m, int n, size_t bytes) {
+  if (m->es != 2) {
+    for (int r : {256, 128, 64, 32})
+      if (ws_layout(m, r).total <= bytes) return r;
+    return 16;
+  }
+  auto fits = [&](int r) { return prefill_layout(m, r, bytes).total <= bytes; };
+  int lo = 16, hi = std::max(16, std::min((int)align_up((size_t)std::max(n, 1), 16), kPrefillMaxRows));
+  while (lo < hi) {  // the largest multiple of 16 that fits
+    const int mid = (lo + hi + 16) / 32 * 16;
+    if (fits(mid)) lo = mid; else hi = mid - 16;
+  }
+  if (n <= lo && lo <= kMaxPassRows) return lo;
+  int best = lo;
+  double best_us = 1e30;
+  const int k0 = (int)ceil_div(n, lo);
+  for (int k = k0; k < k0 + 4; ++k) {
+    const int r = (int)align_up((size_t)ceil_div(n, k), 16);
+    if (r <= kMaxPassRows && k > k0) break;
+    const double us = k * plan_forward(m, r, prefill_layout(m, r, bytes).part_bytes, false).layer_us();
+    if (us < best_us) {
+      best_us = us;
+      best = r;
+    }
+  }
+  return best;
+}
+
 extern "C" int sdd_kv_prefill(sdd_model* m, sdd_kv* kv, int seq, const int32_t* tokens, int n, void* ws,
                               size_t ws_bytes, sdd_stream_t stream) {
   SDD_REQUIRE(m && kv && tokens, "NULL pointer");
@@ -1693,20 +1762,14 @@ extern "C" int sdd_kv_prefill(sdd_model* m, sdd_kv* kv, int seq, const int32_t* 
   SDD_REQUIRE(n >= 1, "prefill needs at least one token");
   if (n - 1 > kv->max_len) return fail(SDD_ECAPACITY, "prompt of %d tokens exceeds max_len %d", n, kv->max_len);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  // largest chunk whose layout fits the workspace
-  int chunk = 0;
-  for (int r : {256, 128, 64, 32, 16}) {
-    if (ws_layout(m, r).total <= ws_bytes) {
-      chunk = r;
-      break;
-    }
-  }
-  if (chunk == 0) return fail(SDD_ECAPACITY, "workspace too small for prefill");
+  if (ws_layout(m, 16).total > ws_bytes) return fail(SDD_ECAPACITY, "workspace too small for prefill");
+  const int chunk = prefill_chunk(m, n - 1, ws_bytes);
   for (int c0 = 0; c0 < n - 1; c0 += chunk) {
     const int rows = std::min(chunk, n - 1 - c0);
     CallCtx cx;
-    int rc = make_ctx(cx, m, kv, ws, ws_bytes, chunk, st);
+    int rc = make_ctx(cx, m, kv, ws, ws_bytes, 16, st);
     if (rc) return rc;
+    cx.L = prefill_layout(m, chunk, ws_bytes);
     EmbedArgs e{};
     e.prefill = 1;
     e.seq = seq;

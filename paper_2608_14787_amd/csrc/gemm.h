@@ -1,6 +1,7 @@
-// GEMM building blocks shared by the 33-row stream-K kernel (decoder.hip) and
-// the many-row kernel (rows.hip): launch arguments, the fragment-major K/V
-// cache indexing, and the fused epilogues that run on a [rows][C] output tile.
+// GEMM building blocks shared by the 33-row stream-K kernels (decoder.hip) and
+// the many-row kernel (tiles.hip): launch arguments, the fragment-major K/V
+// cache and activation indexing, and the fused epilogues that run on a
+// [rows][C] output tile.
 #pragma once
 
 #include <algorithm>
@@ -67,6 +68,8 @@ struct GemmArgs {
   // only contributed a partial loads into L2 before it ends
   const char* Wn;
   int KTn, Gn, ngn, nwg_n, cn;
+  // many-row kernel: row tiles per column group, column blocks, row blocks, k-ranges per tile
+  int ng, ncb, nrb, ksplit;
 };
 
 template <typename T>
@@ -540,14 +543,17 @@ __device__ void epilogue_logits(const GemmArgs& a, const float* tile, int g, con
   }
 }
 
-// Many-row GEMM (rows.hip): bf16 weights, column groups of 8 or 4 tiles, up to
-// kRowsMaxRows rows [a.m0, a.m0 + a.M) per launch of nblocks workgroups (the
-// stream-K partition of a.G x a.KT units); fused epilogue `epi`.  Partial
-// tiles need kRowsPartBytes per workgroup in a.part.  Returns SDD_OK or
-// SDD_EUNSUPPORTED (other group widths, too many rows).
-constexpr int kRowsMaxTBW = 5;     // row tiles per computing wave
-constexpr int kRowsMaxRows = 288;  // rows per launch: the final tile of 288 x 132 fp32 fits the 160 KB of LDS
-constexpr size_t kRowsPartBytes = (size_t)2 * 2 * kRowsMaxTBW * 8 * 4 * 64 * 16;  // 2 slots x a pair of 8-tile groups
-int launch_gemm_rows(int ng, int epi, const GemmArgs& a, int nblocks, hipStream_t st);
+// Many-row GEMM (tiles.hip): bf16 weights, column groups of 8 or 4 tiles, rows [0, a.M) in one launch; fused
+// epilogue `epi`.  A plan fixes the tile (128 wc columns x 128 rtw / wc rows per workgroup), the number of column and
+// row blocks and the k-split.
+struct TilePlan {
+  int wc, rtw;            // wave columns (1 or 2) of the workgroup's 8 waves, row tiles per wave
+  int ncb, nrb, ksplit;   // column blocks, row blocks, k-ranges per tile
+  double us;              // estimated time
+};
+// Best plan for M rows of a matrix of plan `mp` on n_cu compute units, with `part_bytes` for split partials and
+// arrival counters for max_split tiles.
+TilePlan plan_tiles(const MatPlan& mp, int M, int n_cu, size_t part_bytes, int64_t max_split);
+int launch_gemm_tiles(const TilePlan& p, int epi, GemmArgs a, hipStream_t st);
 
 }  // namespace sdd

@@ -171,11 +171,15 @@ struct RowInfo {
 // Per-call workspace carve-up for up to max_rows rows.
 struct WsLayout {
   size_t rowinfo, x, xa, ss_part, q, ao, ffh, part, cnt, amax, total;
+  size_t part_bytes;  // of the partial tiles
   int mp;         // padded rows
   int max_groups; // column groups of the widest GEMM
   int n_wg;       // GEMM workgroups
 };
 
 WsLayout ws_layout(const sdd_model* m, int max_rows);
+// The layout of a prefill chunk of `rows` rows in a workspace of `bytes`: no argmax records, and everything past
+// the rows' buffers holds partial tiles.  total > bytes: the chunk does not fit.
+WsLayout prefill_layout(const sdd_model* m, int rows, size_t bytes);
 
 }  // namespace sdd
