@@ -12,6 +12,7 @@
 //   per layer:   gemm<QKV>   fused q/k/v projection; epilogue: row scale, per-head
 //                            QK RMSNorm, rotate-half RoPE, K/V append to the cache
 //                attention   causal GQA attention of the block rows over the cache
+//                            (attn_prefill.hip for the chunks of a long prompt)
 //                gemm<RESID> output projection + residual; epilogue also writes the
 //                            next GEMM input and the next RMSNorm row scale
 //                gemm<SWIGLU> fused gate/up projection; epilogue silu(gate) * up
@@ -1448,8 +1449,20 @@ static ForwardPlans plan_forward(const sdd_model* m, int M, size_t part_bytes, b
   return p;
 }
 
-// Forward of M rows whose RowInfo/x/xa/sum of squares were written by embed_kernel.
-static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argmax) {
+// Whether one layer's attention of a prefill chunk of R rows that ends at position `npos` takes the prefill kernel.
+// That kernel walks the positions in sequence, about 7 us + 0.8 us per 32-position step while it does not fill the
+// chip; the block kernel splits them over its waves, about 13 us + 0.83 us per step and 16000 (row, query head)
+// pairs.  Measured, prefill against block kernel (us per launch, Qwen3-32B / Qwen2.5-7B heads): 66 rows at position 0
+// 10 / 10 against 17 / 15, 1024 rows 44 / 37 against 153 / 131, 4096 rows 344 / 168 against 1072 / 913, 1000 rows
+// of a 4000-token prompt 100 / 86 against 266 / 294; 95 rows of it 60 against 36, hence the line.
+static bool prefill_attention(const sdd_model* m, int R, int npos) {
+  const double steps = ceil_div(npos, 32);
+  return m->es == 2 && R > kMaxBlockRows && 0.8 * steps <= 6.0 + steps * R * m->cfg.n_q_heads / 19200.0;
+}
+
+// Forward of nb blocks of R rows whose RowInfo/x/xa/sum of squares were written by embed_kernel.  prefill_end: the
+// position after a prefill chunk's last row (one block), 0 for a verify call.
+static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argmax, int prefill_end = 0) {
   const int M = nb * R;
   sdd_model* m = cx.m;
   sdd_kv* kv = cx.kv;
@@ -1488,7 +1501,24 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
       if ((rc = run_gemm(cx, EPI_QKV, PROF_GEMM_QKV, Ly.qkv, hq + 2 * hk, (int)d, xa, a, M, m->ng_qkv, tp.qkv, &nx))) return rc;
     }
     // attention
-    if (m->es == 2) {
+    if (prefill_end > 0 && prefill_attention(m, R, prefill_end)) {
+      AttnPrefillArgs a{};
+      a.q = reinterpret_cast<const uint16_t*>(ws + L.q);
+      a.kc = reinterpret_cast<const uint16_t*>(kv->k + (size_t)l * kv->layer_stride);
+      a.vc = reinterpret_cast<const uint16_t*>(kv->v + (size_t)l * kv->layer_stride);
+      a.out = reinterpret_cast<uint16_t*>(ws + L.ao);
+      a.rows = reinterpret_cast<const RowInfo*>(ws + L.rowinfo);
+      a.R = R;
+      a.hq = c.n_q_heads;
+      a.hkv = c.n_kv_heads;
+      a.grp = c.n_q_heads / c.n_kv_heads;
+      a.ld = kv->ld;
+      a.scale = 1.f / sqrtf((float)c.head_dim);
+      prof_begin(PROF_ATTN, cx.st);
+      rc = launch_attention_prefill(a, c.head_dim, cx.st);
+      prof_end(PROF_ATTN, cx.st);
+      if (rc) return rc;
+    } else if (m->es == 2) {
       AttnMfmaArgs a{};
       a.q = reinterpret_cast<const uint16_t*>(ws + L.q);
       a.kc = reinterpret_cast<const uint16_t*>(kv->k + (size_t)l * kv->layer_stride);
@@ -1777,7 +1807,7 @@ extern "C" int sdd_kv_prefill(sdd_model* m, sdd_kv* kv, int seq, const int32_t* 
     e.tokens = tokens + c0;
     e.R = rows;
     if ((rc = launch_embed(cx, e, rows))) return rc;
-    if ((rc = forward_rows(cx, 1, rows, nullptr, nullptr))) return rc;
+    if ((rc = forward_rows(cx, 1, rows, nullptr, nullptr, c0 + rows))) return rc;
   }
   hipLaunchKernelGGL(prefill_finish_kernel, dim3(1), dim3(64), 0, st, kv->len, kv->pending, kv->err, seq, n, tokens,
                      m->cfg.vocab);

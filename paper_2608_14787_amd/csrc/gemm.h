@@ -17,6 +17,7 @@ enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 constexpr int kGemmThreads = 256;
 constexpr int kXcds = 8;  // XCDs of the MI355X (32 CUs each); workgroups go to them round-robin by linear id
 constexpr int kMaxPassRows = 64;  // rows per GEMM pass (TB <= 4 row tiles of 16)
+constexpr int kMaxBlockRows = 65; // rows of one sequence in a verify call (gamma <= 64)
 // Arrival counters of split column groups sit one 128-byte line apart: the groups of a launch finish
 // together, and device-scope atomics on one line serialize.
 constexpr int kCntStride = 32;
@@ -543,6 +544,26 @@ __device__ void epilogue_logits(const GemmArgs& a, const float* tile, int g, con
   }
 }
 
+// A 16-byte-per-lane direct-to-LDS buffer load: lane l's 16 bytes at `lds` + 16 l.
+template <int AUX>
+__device__ inline void load_lds16(__amdgpu_buffer_rsrc_t rs, void* lds, int voffset, int soffset) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(lds), 16, voffset, soffset, 0,
+                                           AUX);
+}
+// s_waitcnt operand: vector memory count <= n (0..63), the other counters unconstrained (gfx9 encoding:
+// vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
+constexpr int kWaitLgkm0 = 0xC07F;  // every LDS operation, nothing else
+constexpr int wait_vmcnt(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
+// A workgroup barrier without a memory fence (a fence would wait for every load in flight); nothing is scheduled
+// across it.
+__device__ inline void phase_barrier() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // Many-row GEMM (tiles.hip): bf16 weights, column groups of 8 or 4 tiles, rows [0, a.M) in one launch; fused
 // epilogue `epi`.  A plan fixes the tile (128 wc columns x 128 rtw / wc rows per workgroup), the number of column and
 // row blocks and the k-split.
@@ -554,6 +575,18 @@ struct TilePlan {
 // Best plan for M rows of a matrix of plan `mp` on n_cu compute units, with `part_bytes` for split partials and
 // arrival counters for max_split tiles.
 TilePlan plan_tiles(const MatPlan& mp, int M, int n_cu, size_t part_bytes, int64_t max_split);
+// Attention of a prefill chunk (attn_prefill.hip, bf16): R rows of one sequence, rows[0, R), over its cache.
+struct AttnPrefillArgs {
+  const uint16_t* q;   // [rows][hq][head_dim]
+  const uint16_t* kc;  // layer base, per (seq, hkv) ld x head_dim elements, fragment-major
+  const uint16_t* vc;
+  uint16_t* out;       // rows of hq * head_dim columns, fragment-major
+  const RowInfo* rows;
+  int R, hq, hkv, grp, ld;
+  float scale;
+  int qblocks, heads_apart;  // set by the launch
+};
+int launch_attention_prefill(AttnPrefillArgs a, int head_dim, hipStream_t st);
 int launch_gemm_tiles(const TilePlan& p, int epi, GemmArgs a, hipStream_t st);
 
 }  // namespace sdd

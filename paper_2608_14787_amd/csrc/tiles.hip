@@ -31,16 +31,6 @@ constexpr int kTileThreads = 512;
 constexpr int kTilePolls = 1 << 11;  // polls for a split item's other contributors (about 2 ms)
 constexpr size_t kTileRing = 148 * 1024;  // LDS for the ring (the rest: row scales and their partial sums)
 
-// A 16-byte-per-lane direct-to-LDS buffer load: lane l's 16 bytes at `lds` + 16 l.
-template <int AUX>
-__device__ inline void load_lds16(__amdgpu_buffer_rsrc_t rs, void* lds, int voffset, int soffset) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(lds), 16, voffset, soffset, 0,
-                                           AUX);
-}
-// s_waitcnt operand: vector memory count <= n (0..63), the other counters unconstrained (gfx9 encoding:
-// vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
-constexpr int kWaitLgkm0 = 0xC07F;  // every LDS operation, nothing else
-constexpr int wait_vmcnt(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
 // A wave's fragments of one k-step from LDS: 8 weight tiles from address aw and RTW row tiles from ax (this lane's 16
 // bytes of the first; tiles 1 KiB apart).  The reads and their wait are one asm block: the compiler cannot tell them
 // from reads of the slots the wave's own direct-to-LDS loads are still filling and would wait for all of those loads.
@@ -145,16 +135,6 @@ __device__ inline void lds_read_frags(u32x4* w, u32x4* x, uint32_t aw, uint32_t 
         : "memory");
   }
 }
-// A workgroup barrier without a memory fence (a fence would wait for every load in flight); nothing is scheduled
-// across it.
-__device__ inline void phase_barrier() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 // ---- epilogues of one row tile in the accumulator layout --------------------------------------------------
 // v[nt][e]: row `m`, column 16 (ct + nt) + 4 (lane / 16) + e.  No contraction: a row rounds alike everywhere.
 
