@@ -69,8 +69,9 @@ struct GemmArgs {
   // only contributed a partial loads into L2 before it ends
   const char* Wn;
   int KTn, Gn, ngn, nwg_n, cn;
-  // many-row kernel: row tiles per column group, column blocks, row blocks, k-ranges per tile
-  int ng, ncb, nrb, ksplit;
+  // many-row kernel: column tiles per column group, column blocks (the first ncb1 not split), row blocks, k-ranges per
+  // split tile
+  int ng, ncb, ncb1, nrb, ksplit;
 };
 
 template <typename T>
@@ -566,10 +567,11 @@ __device__ inline void phase_barrier() {
 
 // Many-row GEMM (tiles.hip): bf16 weights, column groups of 8 or 4 tiles, rows [0, a.M) in one launch; fused
 // epilogue `epi`.  A plan fixes the tile (128 wc columns x 128 rtw / wc rows per workgroup), the number of column and
-// row blocks and the k-split.
+// row blocks and what is split over k.
 struct TilePlan {
   int wc, rtw;            // wave columns (1 or 2) of the workgroup's 8 waves, row tiles per wave
-  int ncb, nrb, ksplit;   // column blocks, row blocks, k-ranges per tile
+  int ncb, nrb;           // column blocks, row blocks
+  int ncb1, ksplit;       // column blocks that are not split, k-ranges per tile of the others
   double us;              // estimated time
 };
 // Best plan for M rows of a matrix of plan `mp` on n_cu compute units, with `part_bytes` for split partials and

@@ -18,6 +18,8 @@
 //    tiles leave compute units idle, K is split: partials go through 16-byte device-coherent stores and are added
 //    in split order, the tile's row tiles shared out among its contributors.  A row's sums depend on its launch's
 //    plan but not on the other rows' values.
+//  - tiles that fill the chip several times and leave a few over pay a whole round for those few: the column blocks of
+//    the whole rounds run unsplit, those left over follow in the same launch with K split over all compute units.
 // Measured (Qwen3-32B width, with the chunked launches of 288 rows and 4 loading waves this kernel replaced): gate/up
 // over 1024 rows 4 x 148 -> 498 us (1.08 PFLOP/s; the library's product at this size 0.99), over 264 rows 186 -> 151;
 // down 125 -> 89, qkv 76 -> 58, o_proj 45 -> 47, LM head 546 -> 463 us.  What bounds it: a k-step of 8 + RTW fragment
@@ -294,7 +296,11 @@ __device__ inline void tile_qkv(const GemmArgs& a, const f32x4* v, int h, int m,
   }
 }
 
-template <int WC, int RTW, int EPI, bool SPLIT>
+// MODE: what a launch's items are.  (A kernel that holds both kinds of item spills registers in its epilogues, outside
+// the k-loop, so the launches of one kind keep kernels of their own.)
+enum Mode { UNSPLIT = 0, SPLIT = 1, MIXED = 2 };
+
+template <int WC, int RTW, int EPI, int MODE>
 __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) {
   constexpr int NTW = 8, WR = 8 / WC, CG = NTW * WC, RT = WR * RTW, ROWS = 16 * RT;
   constexpr int kStage = (CG + RT) * 1024;
@@ -312,9 +318,10 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
   const bool lateh = wv >= 4;            // the half that runs half a k-step behind
   // item: column block and k-split cs (one XCD's items are 8 apart), row block fastest within an XCD
   const int slot = blockIdx.x / kXcds, cs = blockIdx.x % kXcds + kXcds * (slot / a.nrb), rb = slot % a.nrb;
-  if (cs >= a.ncb * a.ksplit) return;
-  const int cb = cs / a.ksplit, sp = cs % a.ksplit;
-  const int kb = (int)((int64_t)a.KT * sp / a.ksplit), nk = (int)((int64_t)a.KT * (sp + 1) / a.ksplit) - kb;
+  if (cs >= a.ncb1 + (a.ncb - a.ncb1) * a.ksplit) return;
+  const int S = MODE == SPLIT || (MODE == MIXED && cs >= a.ncb1) ? a.ksplit : 1;  // the first ncb1 column blocks are not split
+  const int cb = S == 1 ? cs : a.ncb1 + (cs - a.ncb1) / S, sp = S == 1 ? 0 : (cs - a.ncb1) % S;
+  const int kb = (int)((int64_t)a.KT * sp / S), nk = (int)((int64_t)a.KT * (sp + 1) / S) - kb;
   const int row0 = rb * ROWS, nrows = min(ROWS, a.M - row0);
   const uint32_t KT = (uint32_t)a.KT, G = (uint32_t)a.G, SC = (uint32_t)a.segc, NW = (uint32_t)a.n_wg;
   const int ng = a.ng, unit_b = ng * 1024;
@@ -495,23 +502,28 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
     else
       f(std::integral_constant<int, 4>{});
   };
-  if constexpr (!SPLIT) {
+  if (MODE == UNSPLIT || (MODE == MIXED && S == 1)) {
     with_nt([&](auto ntc) {
 #pragma unroll
       for (int j = 0; j < RTW; ++j)
-        if (wr * RTW + j < ntiles) epilogue(ntc, acc[j], wr * RTW + j, wc);
+        if (wr * RTW + j < ntiles) {
+          epilogue(ntc, acc[j], wr * RTW + j, wc);
+          if constexpr (MODE == MIXED) __builtin_amdgcn_sched_barrier(0);  // one row tile's loads at a time: registers
+        }
     });
     return;
-  } else {
+  }
+  if constexpr (MODE != UNSPLIT) {
 
   // Split item: every contributor stores its accumulators (16-byte device-coherent stores) and the item is
   // finished in ksplit shares of (row tile, wave column) units, each summed in split order.  A contributor waits
   // for the others for a bounded time (a split launch has at most one workgroup per compute unit, so all of them
   // are normally running) and finishes its own share; whoever arrives last also takes the shares that nobody
   // claimed, so the item completes whether or not the others waited.  The last one to leave zeroes the counters.
+  // (Unsplit items, launched first, wait for nobody, so the split ones behind them are always reached.)
   // Measured against the last arriver adding all partials: 264 rows of down_proj 125 -> 93 us, o_proj 61 -> 50.
   const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(a.part, 0, 0x7fffffff, kBufferRsrcWord3);
-  const int item = rb * a.ncb + cb, S = a.ksplit;
+  const int item = rb * (a.ncb - a.ncb1) + cb - a.ncb1;
   auto part_off = [&](int sq, int rt, int wcol) {  // bytes (< 2^31: checked on the host)
     return (((item * S + sq) * RT + rt) * WC + wcol) * NTW * 1024 + lane * 16;
   };
@@ -582,39 +594,50 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
   }
 }
 
-template <int EPI, bool SPLIT>
+template <int EPI, int MODE>
 void launch_shape(const TilePlan& p, const GemmArgs& a, hipStream_t st) {
-  const dim3 grid(kXcds * (int)ceil_div((int64_t)p.ncb * p.ksplit, kXcds) * p.nrb), block(kTileThreads);
+  const dim3 grid(kXcds * (int)ceil_div(p.ncb1 + (int64_t)(p.ncb - p.ncb1) * p.ksplit, kXcds) * p.nrb), block(kTileThreads);
 #define SDD_TILE(WC, RTW) \
-  case WC * 10 + RTW: hipLaunchKernelGGL((gemm_tile_kernel<WC, RTW, EPI, SPLIT>), grid, block, 0, st, a); break
+  case WC * 10 + RTW: hipLaunchKernelGGL((gemm_tile_kernel<WC, RTW, EPI, MODE>), grid, block, 0, st, a); break
   switch (p.wc * 10 + p.rtw) {
-    SDD_TILE(1, 1);
-    SDD_TILE(1, 2);
-    SDD_TILE(1, 3);
     SDD_TILE(2, 2);
     SDD_TILE(2, 3);
     SDD_TILE(2, 4);
-    SDD_TILE(2, 5);
+  }
+  if constexpr (MODE != MIXED) {
+    switch (p.wc * 10 + p.rtw) {
+      SDD_TILE(2, 5);
+      SDD_TILE(1, 1);
+      SDD_TILE(1, 2);
+      SDD_TILE(1, 3);
+    }
   }
 #undef SDD_TILE
 }
 
 template <int EPI>
 void launch_tile(const TilePlan& p, const GemmArgs& a, hipStream_t st) {
-  if (p.ksplit > 1)
-    launch_shape<EPI, true>(p, a, st);
+  if (p.ksplit == 1)
+    launch_shape<EPI, UNSPLIT>(p, a, st);
+  else if (p.ncb1 == 0)
+    launch_shape<EPI, SPLIT>(p, a, st);
   else
-    launch_shape<EPI, false>(p, a, st);
+    launch_shape<EPI, MIXED>(p, a, st);
 }
 
 }  // namespace
 
 // The launch's estimated time, fitted to measurements of every shape and split at 99-1792 rows of the Qwen3-32B and
 // Qwen2.5-7B widths: a k-step takes 0.33 us (two barriers, the LDS reads' latency, load issue) + 14.2 ns per MFMA of
-// a wave; weights stream at 6 TB/s at best; a split writes and reads its partial tiles once at about 6 TB/s and costs
-// 3 us more.
+// a wave; weights stream at 6 TB/s at best, round by round; a split writes and reads its partial tiles once at about
+// 6 TB/s and costs 3 us more, 15 us more again behind unsplit rounds.  Workgroups go to the XCDs round-robin, so rounds
+// and the split workgroups that can run at once are counted per XCD.  (Counted over the whole chip, plans with 33-35
+// waiting workgroups on an XCD of 32 compute units ran into the bound of the wait: down_proj of Qwen2.5-7B over 1136
+// rows 250 -> 152 us, over 528 rows 142 -> 88.)
+// Splitting only the column blocks left over after whole rounds: LM head of 99 rows 338 -> 310 us, gate/up of 1024 rows
+// 474 -> 446 (Qwen3-32B width).  With 5 row tiles per wave that kernel spills in its k-loop and is not used.
 TilePlan plan_tiles(const MatPlan& mp, int M, int n_cu, size_t part_bytes, int64_t max_split) {
-  const int CT = mp.G * mp.ng, RTM = (int)ceil_div(M, 16);
+  const int CT = mp.G * mp.ng, RTM = (int)ceil_div(M, 16), xcd_cus = std::max(1, n_cu / kXcds);
   TilePlan best{};
   best.us = 1e30;
   const size_t cap = std::min<size_t>(part_bytes, (size_t(1) << 31) - 1);
@@ -624,16 +647,28 @@ TilePlan plan_tiles(const MatPlan& mp, int M, int n_cu, size_t part_bytes, int64
     const int wc = sh[0], rtw = sh[1], CG = 8 * wc, RT = 8 / wc * rtw;
     const int ncb = (int)ceil_div(CT, CG), nrb = (int)ceil_div(RTM, RT);
     const double kstep = 0.33 + 0.0142 * 8 * rtw, tile_bytes = 1024.0 * CG * RTM / nrb;
-    for (int s = 1; s <= 16 && s * 8 <= mp.KT; ++s) {
-      const int64_t items = (int64_t)ncb * nrb * s;
-      // (a split launch's workgroups wait for each other: no more than can run at once)
-      if (s > 1 && (items > n_cu || (size_t)items * CG * RT * 1024 > cap || (int64_t)ncb * nrb > max_split)) break;
-      double us = 6.0 + std::max(hbm, (double)ceil_div(items, n_cu) * ((double)ceil_div(mp.KT, s) * kstep + 1.0));
-      if (s == 1)
-        us += tile_bytes / 50e3;  // the last round's epilogue
-      else
-        us += 3.0 + 2.0 * items * tile_bytes / 6.0e6;
-      if (us < best.us) best = TilePlan{wc, rtw, ncb, nrb, s, us};
+    const auto round_us = [&](int s) { return (double)ceil_div(mp.KT, s) * kstep + 1.0; };
+    const auto consider = [&](int ncb1, int s, double us) {
+      if (us < best.us) best = TilePlan{wc, rtw, ncb, nrb, ncb1, s, us};
+    };
+    // the workgroups of n (column block, k-range) pairs on the XCD that gets most of them
+    const auto per_xcd = [&](int64_t n) { return ceil_div(n, kXcds) * nrb; };
+    const int full = (int)(per_xcd(ncb) / xcd_cus);  // whole rounds, each no faster than its weights stream
+    const double full_us = std::max(round_us(1), hbm * xcd_cus / per_xcd(ncb));
+    const double part = hbm - std::min(hbm, full * hbm * xcd_cus / per_xcd(ncb));
+    // (unsplit: the last round's epilogue is exposed)
+    consider(0, 1, 6.0 + full * full_us + (per_xcd(ncb) % xcd_cus ? std::max(part, round_us(1)) : 0.0) + tile_bytes / 50e3);
+    // `rounds` whole rounds of every XCD's compute units unsplit, the column blocks left over split behind them
+    for (int rounds : {0, full}) {
+      const int ncb1 = kXcds * (rounds * xcd_cus / nrb);
+      if (ncb1 >= ncb || (rounds > 0 && (ncb1 == 0 || wc != 2 || rtw > 4))) continue;
+      const int64_t left = ncb - ncb1;
+      for (int s = 2; s <= 16 && s * 8 <= mp.KT; ++s) {
+        // a split tile's workgroups wait for each other: no more of them on an XCD than it can run at once
+        if (per_xcd(left * s) > xcd_cus || (size_t)(left * nrb * s) * CG * RT * 1024 > cap || left * nrb > max_split) break;
+        const double last = std::max(hbm * left / ncb, round_us(s)) + 2.0 * left * nrb * s * tile_bytes / 6.0e6;
+        consider(ncb1, s, 9.0 + (rounds > 0 ? rounds * full_us + 15.0 : 0.0) + last);
+      }
     }
   }
   return best;
@@ -641,6 +676,7 @@ TilePlan plan_tiles(const MatPlan& mp, int M, int n_cu, size_t part_bytes, int64
 
 int launch_gemm_tiles(const TilePlan& p, int epi, GemmArgs a, hipStream_t st) {
   a.ncb = p.ncb;
+  a.ncb1 = p.ncb1;
   a.nrb = p.nrb;
   a.ksplit = p.ksplit;
   switch (epi) {

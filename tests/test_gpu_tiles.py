@@ -95,3 +95,35 @@ def test_prefill_chunks(S, rows):
     ok, rel = row_tol_ok(out[0], out[1], TOL)
     print(f"{rows}: {rel.max():.2e}", flush=True)
     assert ok.all(), rel.max()
+
+
+@pytest.mark.parametrize("n,R", [(3, 33), (5, 33), (16, 64)])
+def test_whole_rounds_then_split(S, n, R):
+    """A vocabulary of 9496 16-column tiles: the LM head's column blocks fill every compute unit twice or more unsplit (2, 3
+    and 4 row tiles per wave), and those left over (the last one only half inside the matrix) follow split over K."""
+    shape = W.ModelShape(1, 4096, 4, 2, 128, 1024, 151936, 1e-6, 1e6, False, "bf16")
+    m = S.Model(shape)
+    m.init_random(7, W.WEIGHT_SIGMA)
+    _run(S, m, shape, n, R, seed=900 + n)
+
+
+def test_whole_rounds_then_split_prefill(S):
+    """A 3000-row chunk at the Qwen3-32B width (qkv, o_proj and down_proj fill the chip once and leave column blocks over)
+    gives the next block that 1000-row chunks give."""
+    shape = W.QWEN32B.with_layers(2)
+    m = S.Model(shape)
+    m.init_random(8, W.WEIGHT_SIGMA)
+    n, R = 3001, 9
+    toks = to_dev_i32(W.prompt(11, n, shape.vocab))
+    drafts = to_dev_i32(W.prompt(12, R - 1, shape.vocab).reshape(1, R - 1))
+    out = []
+    for rows in (4096, 99):
+        kv, ws = S.KVCache(m, 1, n + R), m.workspace(rows)
+        kv.prefill(0, toks, ws)
+        lg = torch.empty((1, R, shape.vocab), device="cuda")
+        kv.verify(to_dev_i32([0]), drafts, lg, None, ws)
+        assert kv.state()[2] == 0
+        out.append(lg[0].cpu().numpy())
+    ok, rel = row_tol_ok(out[0], out[1], TOL)
+    print(f"max rel {rel.max():.2e}", flush=True)
+    assert ok.all(), rel.max()
