@@ -18,6 +18,12 @@
 // dispatched before it: the wait never holds a compute unit that those need.  Hidden activations move
 // through device-coherent stores and loads.  The k-order of every sum is fixed, so results are
 // bit-reproducible.
+//
+// A few dozen positions are bound by this chain's latencies: load, stage and multiply of a chunk, three hand-offs, two
+// dense layers.  One k-chunk per layer-1 workgroup, and dense layers whose operands come from memory in the MFMA's
+// order (weights ahead of the wait, no staging, four accumulators) instead of 64 staged rows and a chain of 64 MFMAs:
+// with the scheduler call 50.0 -> 30.6 us at 32 positions x 3603 inputs, 68.0 -> 40.8 at 128, 372 -> 150 at 528, 711 ->
+// 378 at 1536; error of z against fp64 2.0e-7 -> 1.6e-7 at 32 positions.
 #include "sdd_internal.h"
 
 namespace sdd {
@@ -123,9 +129,11 @@ __device__ void layer1_body(const MlpArgs& a, int bid, float* smem, int* s_flag)
       sX[rsub + 2 * u][kl] = (kin && row < a.n) ? (xv[u] - mu) / sg : 0.f;
     }
     __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < kKc; kk += 4)
-      acc = mfma4(sW[lane % 16][kk + lane / 16], sX[wave * 16 + lane % 16][kk + lane / 16], acc);
+    if (r0 + 16 * wave < a.n) {
+#pragma unroll
+      for (int kk = 0; kk < kKc; kk += 4)
+        acc = mfma4(sW[lane % 16][kk + lane / 16], sX[wave * 16 + lane % 16][kk + lane / 16], acc);
+    }
     __syncthreads();
   }
   // acc[t]: column c0 + 4 (lane / 16) + t, row r0 + 16 wave + lane % 16
@@ -136,18 +144,19 @@ __device__ void layer1_body(const MlpArgs& a, int bid, float* smem, int* s_flag)
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc), prs, off, 0, kCoherentCpol);
   if (!arrive_last(&a.cnt1[tile * kCntLine], a.S, s_flag)) return;
   // last split of this tile: sum the splits in order, bias, GELU
-  // (eight splits' loads in flight at a time, added in split order)
+  // (16 splits' loads in flight at a time, added in split order)
+  constexpr int kB = 16;
   f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < a.S; s0 += 8) {
-    f32x4 pv[8];
+  for (int s0 = 0; s0 < a.S; s0 += kB) {
+    f32x4 pv[kB];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < kB; ++q) {
       const int ss = min(s0 + q, a.S - 1);
       pv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
                                             prs, (((tile * a.S + ss) * kRowTile + row_l) * 16 + col4) * 4, 0, kCoherentCpol));
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
+    for (int q = 0; q < kB; ++q)
       if (s0 + q < a.S) sum += pv[q];
   }
   const int row = r0 + row_l;
@@ -161,56 +170,51 @@ __device__ void layer1_body(const MlpArgs& a, int bid, float* smem, int* s_flag)
   count_done(&a.done1[rt * kCntLine]);
 }
 
+// Layers 2 and 3.  A wave's operands come straight from memory as 16-byte loads: lane 16 g + i holds columns
+// 16 j + 4 g .. + 3 of weight column i and of row i, and MFMA (j, t) contracts element t of both, so a lane group's k is
+// the same on both sides and nothing is staged.  The weights are loaded before the wait for the input rows; the four
+// MFMAs of a j share an accumulator and the j's take four in turn (a serial chain of 16, not 64).
 template <bool LAST>
-__device__ void dense_body(const MlpArgs& a, int bid, const float* hin, const float* W, const float* b, float* hout,
-                           float* smem, int* s_flag) {
-  float (*sW)[kMaxH + 1] = reinterpret_cast<float (*)[kMaxH + 1]>(smem);
-  float (*sX)[kMaxH + 1] = reinterpret_cast<float (*)[kMaxH + 1]>(smem + 16 * (kMaxH + 1));
+__device__ void dense_body(const MlpArgs& a, int bid, const int* ready, const float* hin, const float* W, const float* b,
+                           float* hout, int* s_flag) {
+  constexpr int J = kMaxH / 16;
   const int CT = a.H / 16;
   const int ct = bid % CT, rt = bid / CT;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const int c0 = ct * 16, r0 = rt * kRowTile, H = a.H;
-  // stage the weight slice [16][H] and the input rows [64][H] with 16-byte loads, all issued before use
-  // (H is a multiple of 16: a row is H / 4 float4s)
-  const int H4 = H / 4;
-  f32x4 wv[kMaxH / 64], xv[kMaxH / 4];
+  const float* wp = W + (int64_t)(c0 + lane % 16) * H + 4 * (lane / 16);
+  f32x4 wv[J], xv[J];
 #pragma unroll
-  for (int u = 0; u < kMaxH / 64; ++u) {
-    const int i = tid + kMlpThreads * u;
-    wv[u] = i < 16 * H4 ? *reinterpret_cast<const f32x4*>(W + (int64_t)(c0 + i / H4) * H + 4 * (i % H4)) : f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < J; ++j) wv[j] = *reinterpret_cast<const f32x4*>(wp + 16 * min(j, CT - 1));
+  float bv[4], w4v[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    bv[t] = b[c0 + 4 * (lane / 16) + t];
+    w4v[t] = LAST ? a.w4[c0 + 4 * (lane / 16) + t] : 0.f;
   }
-  // the input rows were written by other workgroups of this launch: device-coherent loads
-  const __amdgpu_buffer_rsrc_t irs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(hin), 0, 0x7fffffff,
-                                                                       kBufferRsrcWord3);
+  if (!wait_count(&ready[rt * kCntLine], CT, s_flag) && tid == 0) atomicOr(a.err, 1);
+  f32x4 acc[4];
 #pragma unroll
-  for (int u = 0; u < kMaxH / 4; ++u) {
-    const int i = tid + kMlpThreads * u, r = i / H4;
-    xv[u] = (i < kRowTile * H4 && r0 + r < a.n)
-                ? __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                irs, ((r0 + r) * H + 4 * (i % H4)) * 4, 0, kCoherentCpol))
-                : f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (r0 + 16 * wave < a.n) {
+    // the input rows were written by other workgroups of this launch: device-coherent loads (rows past n read zero)
+    const __amdgpu_buffer_rsrc_t irs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(hin), 0, a.n * H * 4,
+                                                                         kBufferRsrcWord3);
+    const int off = ((r0 + 16 * wave + lane % 16) * H + 4 * (lane / 16)) * 4;
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      xv[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(irs, off, 64 * min(j, CT - 1), kCoherentCpol));
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (j < CT)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[j % 4] = mfma4(wv[j][t], xv[j][t], acc[j % 4]);
   }
-#pragma unroll
-  for (int u = 0; u < kMaxH / 64; ++u) {
-    const int i = tid + kMlpThreads * u;
-    if (i < 16 * H4)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sW[i / H4][4 * (i % H4) + e] = wv[u][e];
-  }
-#pragma unroll
-  for (int u = 0; u < kMaxH / 4; ++u) {
-    const int i = tid + kMlpThreads * u;
-    if (i < kRowTile * H4)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sX[i / H4][4 * (i % H4) + e] = xv[u][e];
-  }
-  __syncthreads();
-  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int kk = 0; kk < H; kk += 4) acc = mfma4(sW[lane % 16][kk + lane / 16], sX[wave * 16 + lane % 16][kk + lane / 16], acc);
+  const f32x4 sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   const int row_l = wave * 16 + lane % 16, col4 = 4 * (lane / 16), row = r0 + row_l;
   float hv[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) hv[t] = gelu_erf(acc[t] + b[c0 + col4 + t]);
+  for (int t = 0; t < 4; ++t) hv[t] = gelu_erf(sum[t] + bv[t]);
   if constexpr (!LAST) {
     const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(hout, 0, 0x7fffffff, kBufferRsrcWord3);
     if (row < a.n)
@@ -219,7 +223,7 @@ __device__ void dense_body(const MlpArgs& a, int bid, const float* hin, const fl
     count_done(&a.done2[rt * kCntLine]);
   } else {
     // this tile's share of w4 . h3 for the row: the lane's 4 columns in order, then the 4 lane groups in order
-    const float zs = dot4(hv, a.w4 + c0 + col4);
+    const float zs = dot4(hv, w4v);
     const float z1 = __shfl(zs, lane % 16 + 16), z2 = __shfl(zs, lane % 16 + 32), z3 = __shfl(zs, lane % 16 + 48);
     const float tz = ((zs + z1) + z2) + z3;  // lanes 0..15: rows 16 wave + lane
     const __amdgpu_buffer_rsrc_t zrs = __builtin_amdgcn_make_buffer_rsrc(a.zpart, 0, 0x7fffffff, kBufferRsrcWord3);
@@ -253,7 +257,7 @@ __device__ void dense_body(const MlpArgs& a, int bid, const float* hin, const fl
 }
 
 __global__ void __launch_bounds__(kMlpThreads) survival_kernel(MlpArgs a) {
-  __shared__ __attribute__((aligned(16))) float smem[(16 + kRowTile) * (kMaxH + 1)];
+  __shared__ __attribute__((aligned(16))) float smem[(16 + kRowTile) * (kKc + 1)];
   __shared__ int s_flag;
   const int CT = a.H / 16, RT = (a.n + kRowTile - 1) / kRowTile;
   const int n1 = RT * CT * a.S, n2 = RT * CT;
@@ -261,13 +265,9 @@ __global__ void __launch_bounds__(kMlpThreads) survival_kernel(MlpArgs a) {
   if (bid < n1) {
     layer1_body(a, bid, smem, &s_flag);
   } else if (bid < n1 + n2) {
-    const int b2 = bid - n1;
-    if (!wait_count(&a.done1[(b2 / CT) * kCntLine], CT, &s_flag) && threadIdx.x == 0) atomicOr(a.err, 1);
-    dense_body<false>(a, b2, a.h1, a.W2, a.b2, a.h2, smem, &s_flag);
+    dense_body<false>(a, bid - n1, a.done1, a.h1, a.W2, a.b2, a.h2, &s_flag);
   } else {
-    const int b3 = bid - n1 - n2;
-    if (!wait_count(&a.done2[(b3 / CT) * kCntLine], CT, &s_flag) && threadIdx.x == 0) atomicOr(a.err, 1);
-    dense_body<true>(a, b3, a.h2, a.W3, a.b3, nullptr, smem, &s_flag);
+    dense_body<true>(a, bid - n1 - n2, a.done2, a.h2, a.W3, a.b3, nullptr, &s_flag);
   }
 }
 
@@ -295,10 +295,11 @@ MlpWs mlp_ws(int n, int H, int S) {
   return w;
 }
 
-// k-splits of layer 1: about 256 workgroups in all, each split a whole number of LDS chunks
+// k-splits of layer 1: up to 512 workgroups in all (three fit a compute unit), each split a whole number of LDS
+// chunks; for few positions one chunk each, a chunk being a serial load, stage and multiply
 void layer1_splits(int n, int H, int d_in, int& S, int& kc_split) {
   const int RT = (int)ceil_div(n > 0 ? n : 1, kRowTile), CT = H / 16;
-  int want = std::max(1, 256 / (RT * CT));
+  int want = std::max(1, 512 / (RT * CT));
   kc_split = (int)ceil_div(ceil_div(d_in, want), kKc) * kKc;
   S = (int)ceil_div(d_in, kc_split);
 }
