@@ -229,6 +229,58 @@ __device__ __attribute__((always_inline)) inline void stats_update(ThreadStats& 
   // max when greater (or when none is held yet), at the vector's first element equal to it -- the same
   // result as visiting the elements one by one in index order.  kIdx = false (drafter rows, whose argmax is
   // never used) records index 0 instead of searching.
+  if constexpr (VEC > 1) {
+    // Vectors of finite values only (whole waves of them: all but a row's last ones): one or two instructions per
+    // element instead of seven find the maximum and show that nothing is to be left out -- with sums a NaN shows in the
+    // sum and an infinity in the extremes, without them either shows in a sum of zero multiples.  The results are
+    // the general path's (sums up to the rounding of one fused multiply-add).
+    float hi = v[0];
+#pragma unroll
+    for (int t = 1; t < VEC; ++t) hi = fmaxf(hi, v[t]);
+    const float mn = fmaxf(st.mf, hi);
+    float add = 0.f;
+    bool plain;
+    if constexpr (kSum) {
+      float lo = v[0];
+#pragma unroll
+      for (int t = 1; t < VEC; ++t) lo = fminf(lo, v[t]);
+#pragma unroll
+      for (int t = 0; t < VEC; ++t) add += exp_shift(v[t], mn);
+      plain = valid && hi < INFINITY && lo > -INFINITY && add == add;
+    } else {
+#pragma unroll
+      for (int t = 0; t < VEC; ++t) add = __builtin_fmaf(v[t], 0.f, add);
+      plain = valid && add == 0.f;
+    }
+    if (!__builtin_amdgcn_ballot_w64(!plain)) {
+      const bool take = st.a < 0 || hi > st.m;
+      int idx = 0;
+      if (kIdx && __builtin_amdgcn_ballot_w64(take)) {
+#pragma unroll
+        for (int t = VEC - 1; t >= 0; --t) idx = v[t] == hi ? t : idx;
+      }
+      st.m = take ? hi : st.m;
+      st.a = take ? e0 + idx : st.a;
+      if constexpr (kSum) {
+        st.s = st.mf > -INFINITY ? st.s * exp_shift(st.mf, mn) + add : add;
+        st.mf = mn;
+      }
+      if constexpr (kCount) {
+        bool tie = false;
+#pragma unroll
+        for (int t = 0; t < VEC; ++t) {
+          st.cnt += v[t] > zx ? 1 : 0;
+          tie |= v[t] == zx;
+        }
+        if (__builtin_amdgcn_ballot_w64(tie)) {
+#pragma unroll
+          for (int t = 0; t < VEC; ++t) st.cnt += (v[t] == zx && e0 + t < x) ? 1 : 0;
+        }
+      }
+      return;
+    }
+    if (!__builtin_amdgcn_ballot_w64(valid)) return;  // past the chunk's end in every lane
+  }
   float vm = -INFINITY;  // max over finite values (reference of the sum)
   float vx = -INFINITY;  // max over non-NaN values (comparisons with NaN are false)
   float zf[VEC];         // the finite values of a valid vector, -inf elsewhere (exp(-inf - m) adds exactly 0)

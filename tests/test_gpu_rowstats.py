@@ -127,6 +127,35 @@ def test_accept_edge_cases(sdd):
         sdd.accept(torch.from_numpy(d).cuda(), torch.from_numpy(z).cuda(), 3, lenience=0.0)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [8, 4096, 20488])
+def test_non_finite_in_a_stream_of_finite_vectors(sdd, dtype, V):
+    """One NaN, +inf or -inf per row, in the first, an inner or the last vector: the waves that hold it take the general
+    path, the others the one for finite vectors, and both give the oracle's integers in every mode without
+    probabilities, and the confidence's skip lengths."""
+    g = np.random.default_rng(V)
+    B, R = 9, 3
+    z = g.standard_normal((B, R, V)).astype(np.float32)
+    d = g.integers(0, V, size=(B, R - 1)).astype(np.int32)
+    for b in range(B):
+        at = [0, V // 2 + b % 8 if V > 16 else 3, V - 1][b // 3]
+        z[b, 1, at] = [np.nan, np.inf, -np.inf][b % 3]
+        d[b, 0] = z[b, 0].argmax()
+        d[b, 1] = np.nanargmax(z[b, 1]) if b % 2 else at
+    zt = torch.from_numpy(z).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    zv = zt.float().cpu().numpy()
+    for mode, k, len_ in ((0, 1, 1.0), (2, 4, 1.0), (3, 1, 0.3)):
+        L, nxt, fl = sdd.accept(torch.from_numpy(d).cuda(), zt, mode, k=k, lenience=len_)
+        ref = oracle.accept(mode, d, zv, k=k, lenience=len_)
+        assert L.cpu().tolist() == ref["accepted_len"].tolist(), mode
+        assert nxt.cpu().tolist() == ref["next_token"].tolist(), mode
+        assert fl.cpu().tolist() == ref["flags"].tolist(), mode
+    sk, lc, _ = sdd.confidence_prefix(zt, R, 0.5 / V, log_conf=True)
+    ref = oracle.confidence_prefix(zv, R, 0.5 / V)
+    assert sk.cpu().tolist() == ref["skip_len"].tolist()
+    np.testing.assert_allclose(lc.cpu().numpy()[:, [0, 2]], ref["log_conf"][:, [0, 2]], atol=2e-5, rtol=0)
+
+
 @pytest.mark.parametrize("variant", ["literal", "boosted"])
 def test_confidence_full_size(sdd, variant):
     B, gamma, V = 16, 32, 151936
