@@ -37,30 +37,51 @@ namespace sdd {
 // row; max value, lowest index among equal maxima (NaN never wins).
 __global__ void __launch_bounds__(256) row_argmax_kernel(const float* amax_v, const int* amax_i, int G, int mp,
                                                         const RowInfo* rows, int32_t* out) {
-  __shared__ float sv[256];
-  __shared__ int si[256];
+  __shared__ float sv[4];
+  __shared__ int si[4];
   const int m = blockIdx.x, t = threadIdx.x;
+  const int valid = rows[m].valid;
   float bv = -INFINITY;
   int bi = -1;
-  for (int g = t; g < G; g += 256) {
-    const float v = amax_v[(int64_t)g * mp + m];
-    const int i = amax_i[(int64_t)g * mp + m];
-    if (arg_better(v, i, bv, bi)) {
-      bv = v;
-      bi = i;
+  constexpr int kB = 5;  // candidates in flight (past the end the last one again, which changes nothing)
+  for (int g0 = t; g0 < G; g0 += 256 * kB) {
+    float v[kB];
+    int i[kB];
+#pragma unroll
+    for (int j = 0; j < kB; ++j) {
+      const int64_t at = (int64_t)min(g0 + 256 * j, G - 1) * mp + m;
+      v[j] = amax_v[at];
+      i[j] = amax_i[at];
+    }
+#pragma unroll
+    for (int j = 0; j < kB; ++j)
+      if (arg_better(v[j], i[j], bv, bi)) {
+        bv = v[j];
+        bi = i[j];
+      }
+  }
+#pragma unroll
+  for (int o = 1; o < kWave; o *= 2) {
+    const float v2 = __shfl_xor(bv, o);
+    const int i2 = __shfl_xor(bi, o);
+    if (arg_better(v2, i2, bv, bi)) {
+      bv = v2;
+      bi = i2;
     }
   }
-  sv[t] = bv;
-  si[t] = bi;
+  if (t % kWave == 0) {
+    sv[t / kWave] = bv;
+    si[t / kWave] = bi;
+  }
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o && arg_better(sv[t + o], si[t + o], sv[t], si[t])) {
-      sv[t] = sv[t + o];
-      si[t] = si[t + o];
-    }
-    __syncthreads();
+  if (t == 0 && valid) {
+    for (int w = 1; w < 4; ++w)
+      if (arg_better(sv[w], si[w], bv, bi)) {
+        bv = sv[w];
+        bi = si[w];
+      }
+    out[m] = bi < 0 ? 0 : bi;
   }
-  if (t == 0 && rows[m].valid) out[m] = si[0] < 0 ? 0 : si[0];
 }
 
 template <typename T, int TB, int NG, int EPI>

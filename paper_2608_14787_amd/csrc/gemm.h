@@ -106,25 +106,26 @@ __device__ inline int64_t vfrag_index(int p, int d, int HD) {
 }
 
 // GEMM inputs (the normed residual stream, the attention output, the FFN hidden rows) are fragment-major
-// too: 1 KiB tiles of 16 rows x 32 bf16 (16 fp32) columns in the order an MFMA B operand takes
-// them, tile (row tile, k-tile) at (row tile * KT + k-tile) KiB, lane 16 g + rho of a tile holding row rho and
-// the EPL = 16 / sizeof(T) columns from g EPL.
+// too: 1 KiB tiles of 16 rows x 32 bf16 (16 fp32) columns, what one fragment load of an MFMA B operand takes, tile
+// (row tile, k-tile) at (row tile * KT + k-tile) KiB; inside a tile row after row, 64 bytes each, of which lane
+// 16 g + rho loads the EPL = 16 / sizeof(T) columns from g EPL of row rho.
 // Why: a fragment load of row-major activations touched 16 lines and used half of each, and every column group
 // re-reads them; as one contiguous KiB the same loads take half the line requests.  Measured (Qwen3-32B width,
 // 2 layers + LM head, before -> after): 1056-token recompute 4.43 -> 3.74 ms, 264-row verify 1.78 -> 1.59 ms, 99
-// rows 981 -> 896 us; 33 rows (4 layers) 1098 -> 1072 us; a 1-row step pays 4 lines per fragment instead of 1
-// (Qwen2.5-7B width, 4 layers: 600.6 -> 603.3 us).
+// rows 981 -> 896 us; 33 rows (4 layers) 1098 -> 1072 us.  Rows inside a tile rather than the lanes' order, in which a
+// tile of one row (a decode step, the 33rd row of a block) took 4 lines instead of 1: 33 rows 1074 -> 1068 us
+// (Qwen2.5-7B width 707 -> 703), a 1-row step 604 -> 601 us (row-major: 599), with the row argmax's loads batched.
 // Element index of (row, col); EPL consecutive columns from a multiple of EPL are contiguous (16 bytes).
 template <typename T>
 __device__ inline int64_t xfrag_index(int row, int col, int KT) {
   constexpr int EPL = 16 / (int)sizeof(T), KTL = 4 * EPL;
-  return ((int64_t)(row / 16) * KT + col / KTL) * (64 * EPL) + ((col % KTL) / EPL * 16 + row % 16) * EPL + col % EPL;
+  return ((int64_t)(row / 16) * KT + col / KTL) * (64 * EPL) + row % 16 * KTL + col % KTL;
 }
 // Byte offset of this lane's 16 bytes of the fragment (row tile, k-tile 0) for a buffer load; lanes of rows at
 // or past `rows` get an offset past every descriptor (rows pad to whole tiles; a padded row's lanes read zero
 // without a memory access).
 __device__ inline int xfrag_lane(int row_tile, int KT, int rows, int lane) {
-  return 16 * row_tile + lane % 16 < rows ? row_tile * KT * 1024 + lane * 16 : 0x7ffffff0;
+  return 16 * row_tile + lane % 16 < rows ? row_tile * KT * 1024 + lane % 16 * 64 + lane / 16 * 16 : 0x7ffffff0;
 }
 // bytes of whole row tiles holding `rows` rows: the range of a descriptor over them
 __device__ inline int xfrag_bytes(int rows, int KT) { return (rows + 15) / 16 * KT * 1024; }
