@@ -24,6 +24,8 @@
 // order (weights ahead of the wait, no staging, four accumulators) instead of 64 staged rows and a chain of 64 MFMAs:
 // with the scheduler call 50.0 -> 30.6 us at 32 positions x 3603 inputs, 68.0 -> 40.8 at 128, 372 -> 150 at 528, 711 ->
 // 378 at 1536; error of z against fp64 2.0e-7 -> 1.6e-7 at 32 positions.
+#include <algorithm>
+
 #include "sdd_internal.h"
 
 namespace sdd {
@@ -321,9 +323,13 @@ extern "C" int sdd_survival_workspace_bytes(const sdd_mlp* m, int n, size_t* byt
   int rc = check_mlp(m);
   if (rc) return rc;
   SDD_REQUIRE(bytes != nullptr && n >= 0, "bad arguments");
-  int S, kc;
-  layer1_splits(n, m->H, m->d_hid + m->n_sc, S, kc);
-  *bytes = mlp_ws(n, m->H, S).total;
+  // fewer positions take more k-splits and can need more: a workspace for n serves every smaller call
+  *bytes = 0;
+  for (int64_t k = n; k > -kRowTile; k -= kRowTile) {
+    int S, kc;
+    layer1_splits((int)std::max<int64_t>(k, 1), m->H, m->d_hid + m->n_sc, S, kc);
+    *bytes = std::max(*bytes, mlp_ws((int)std::max<int64_t>(k, 1), m->H, S).total);
+  }
   return SDD_OK;
 }
 

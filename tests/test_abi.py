@@ -239,3 +239,16 @@ def test_pair_partition_reads_every_stored_tile(S, which):
                 u += ke - kb
         assert (seen == 1).all(), kind
     assert L.sdd_model_destroy(h) == S.OK
+
+
+@pytest.mark.parametrize("d_in,H", [(3603, 256), (1043, 256), (3603, 64), (40, 16)])
+def test_survival_workspace_serves_every_smaller_call(S, d_in, H):
+    """The predictor's k-splits fall as positions rise; the workspace size must not."""
+    P = C.c_void_p(4096)  # never read: only the sizes are
+    desc = S.MlpDesc(d_in - 19, 19, H, *[P] * 9, 0.0)
+    last = 0
+    for n in list(range(1, 1300, 31)) + [4096]:
+        out = C.c_size_t()
+        assert S.lib().sdd_survival_workspace_bytes(C.byref(desc), n, C.byref(out)) == 0
+        assert out.value >= last, n
+        last = out.value
