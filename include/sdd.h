@@ -164,8 +164,13 @@ int sdd_workspace_init(void* ws, size_t bytes, sdd_stream_t stream);
 
 /* Prefill of sequence seq with tokens[0..n) (device int32): caches positions
  * 0..n-2, sets len = n-1 and pending = tokens[n-1].  The prompt is processed
- * in equal row chunks, as few and as large as the workspace's bytes hold (at
- * most 4096 rows; fp32 models: at most 256 and max_rows).
+ * in row chunks, as few as the workspace's bytes hold (bf16: at most 4096 rows;
+ * a larger workspace makes them fewer and faster).  Bits: rows go in passes of
+ * the largest of 256, 128, 64, 32, 16 rows whose sdd_workspace_bytes the
+ * workspace holds; the rows of a pass of more than 64 rows and those of a
+ * smaller one (a small workspace's, or the last pass) are summed in two
+ * orders (sdd_verify_block, below), and nothing else of the chunks or the
+ * workspace shows in the cache: workspaces for 256 rows or more give the same.
  * The verifier KV cache is this library's reading of the verify call: the
  * paper's own verifier keeps no cache and recomputes the whole sequence every
  * call (Appendix "Evaluation and Throughput"; sdd_verify_full is that mode).
@@ -187,7 +192,11 @@ int sdd_kv_prefill(sdd_model* m, sdd_kv* kv, int seq, const int32_t* tokens, int
  * the rows are written at len..len+gamma but len is unchanged until
  * sdd_kv_commit.  gamma = 0 is a plain decode step.  Sequences whose cache
  * cannot hold the block are refused on the device (sticky error bit0; their
- * outputs are left unwritten).  Requires n_seq*(gamma+1) <= max_rows of ws. */
+ * outputs are left unwritten).  Requires n_seq*(gamma+1) <= max_rows of ws.
+ * Bits: a row's outputs depend on its sequence alone, not on the other
+ * sequences or rows of the call, except (bf16) for one line: calls of up to 64
+ * rows in all and calls of more add a row's products in different orders, and
+ * their results differ by rounding. */
 int sdd_verify_block(sdd_model* m, sdd_kv* kv, const int32_t* seq_ids, int n_seq,
                      const int32_t* drafts, int gamma, float* logits, int32_t* argmax,
                      void* ws, size_t ws_bytes, sdd_stream_t stream);

@@ -3,61 +3,34 @@
 //
 // The block-verification kernel gives 16 query vectors a workgroup and streams the cache through every workgroup's
 // registers: right for the few queries of a verified block, but with a chunk's thousands it is bound by the L2's
-// bandwidth (512 bytes of K/V per 16 queries and position).  Here a workgroup of 4 waves takes 128 consecutive query
-// vectors (rows x the heads that share a KV head), 32 per wave, and walks the positions in 32-position steps whose K
-// and V go to LDS once for all four (direct-to-LDS loads, a ring of kRing steps; the cache's fragment-major blocks are
-// the MFMA operands, so LDS reads are contiguous and conflict-free).  A wave holds its queries, its 32 x HD output
-// accumulators and one step's operands in registers: two workgroups per CU, so that one's softmax runs beside the
-// other's MFMAs.  The softmax is online, in base 2 with the scale folded into one multiply-add; the accumulators are
-// rescaled only in steps where some query's maximum rises (the factor is 1 otherwise), and positions are masked only
-// in the steps that reach a wave's diagonal.  Later query blocks see more positions and are launched first.
-// Measured (Qwen3-32B heads, one layer, block kernel -> this): 1024 rows at position 0 153 -> 44 us, 4096 rows 1072 ->
-// 344 us (0.2 -> 0.8 PFLOP/s of the unmasked half).  What bounds it: per 32-position step and SIMD, two waves' 64 MFMAs (0.45 us)
-// and their softmax on the vector units take 1.3 us; alone on a CU a workgroup's step takes 0.8 us, a serial chain
-// of LDS reads, MFMAs, exponentials and MFMAs.
+// bandwidth (512 bytes of K/V per 16 queries and position).  This kernel computes the same results bit for bit (so a
+// row's cached K/V do not depend on the chunk it was computed in): wave w takes the 32-position steps w, w + 8, ... in
+// order, and the waves' partial results are added in wave order, per query in the same operations.  But a workgroup
+// holds kQT tiles of 16 query vectors (rows x the heads that share a KV head), so that a step's K and V, loaded once
+// into a wave's registers, serve kQT times as many.  A step's K registers take the next step's as soon as the tiles'
+// scores are computed, and the V registers after the last product; the queries' fragments sit in LDS.
+// Positions are masked only in the steps that reach a tile's diagonal, accumulators rescaled only where some query's
+// maximum rises (the factor is 1 otherwise).  Later query blocks see more positions and are launched first.
+// Measured, block kernel -> this, one layer of a prompt in one chunk (Qwen3-32B / Qwen2.5-7B heads): 66-96 rows 18 / 17 ->
+// 12 / 12 us, 256 rows 35 / 35 -> 21 / 14, 1024 rows 156 / 136 -> 78 / 41, 4096 rows 1092 / 905 -> 623 / 268.  What bounds it:
+// a wave takes 1.8 us per step of three tiles, 0.3 us of them MFMAs: the softmax on the vector units, with two waves per
+// SIMD to cover the loads (three tiles take 244 registers; four spill); below a thousand rows a workgroup's start and the
+// combination of its waves.  Sharing a step's K/V between waves through LDS (a wave per 32 queries, positions in one
+// sequence) takes 42 us for 1024 rows and 356 for 4096, but adds a query's positions in another order.
 #include "gemm.h"
 
 namespace sdd {
 namespace {
 
-constexpr int kWaves = 4, kThreads = kWaves * kWave;
-constexpr int kQT = 2;                           // query tiles of 16 per wave
-constexpr int kQueries = kWaves * kQT * 16;      // query vectors per workgroup
-constexpr int kRing = 4;                         // steps in LDS
+constexpr int kWaves = kAttnWaves, kThreads = kWaves * kWave;
 
-// One step's K and V fragments from LDS address `a` (this lane's 16 bytes of the first block; 1 KiB apart).  The
-// reads and their wait are one asm block: the compiler cannot tell them from reads of the slots that direct-to-LDS
-// loads are still filling and would wait for all of those loads.
-#define SDD_RD(o, a, ofs) "ds_read_b128 %" #o ", %" #a " offset:" #ofs "\n\t"
-template <int HD>
-__device__ inline void read_step(u32x4* f, uint32_t a) {
-  if constexpr (HD == 128) {
-    asm volatile(SDD_RD(0, 16, 0) SDD_RD(1, 16, 1024) SDD_RD(2, 16, 2048) SDD_RD(3, 16, 3072) SDD_RD(4, 16, 4096)
-                     SDD_RD(5, 16, 5120) SDD_RD(6, 16, 6144) SDD_RD(7, 16, 7168) SDD_RD(8, 16, 8192) SDD_RD(9, 16, 9216)
-                         SDD_RD(10, 16, 10240) SDD_RD(11, 16, 11264) SDD_RD(12, 16, 12288) SDD_RD(13, 16, 13312)
-                             SDD_RD(14, 16, 14336) SDD_RD(15, 16, 15360) "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]),
-                   "=&v"(f[7]), "=&v"(f[8]), "=&v"(f[9]), "=&v"(f[10]), "=&v"(f[11]), "=&v"(f[12]), "=&v"(f[13]),
-                   "=&v"(f[14]), "=&v"(f[15])
-                 : "v"(a)
-                 : "memory");
-  } else {
-    asm volatile(SDD_RD(0, 8, 0) SDD_RD(1, 8, 1024) SDD_RD(2, 8, 2048) SDD_RD(3, 8, 3072) SDD_RD(4, 8, 4096)
-                     SDD_RD(5, 8, 5120) SDD_RD(6, 8, 6144) SDD_RD(7, 8, 7168) "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7])
-                 : "v"(a)
-                 : "memory");
-  }
-}
-#undef SDD_RD
-
-template <int HD>
-__global__ void __launch_bounds__(kThreads, 2) attention_prefill_kernel(AttnPrefillArgs a) {
-  constexpr int KK = HD / 32, DB = HD / 16, NB = 2 * KK + DB;  // 1 KiB blocks of a step: 2 KK of K, then DB of V
-  constexpr int LQ = NB / kWaves;                              // of them per wave
-  constexpr int kStage = NB * 1024;
-  static_assert(2 * KK == DB && LQ % 2 == 0, "K and V take the same number of loads of each wave");
-  __shared__ __align__(16) char s_ring[kRing * kStage];
+template <int HD, int QT>
+__global__ void __launch_bounds__(kThreads, 1) attention_prefill_kernel(AttnPrefillArgs a) {
+#pragma clang fp contract(off)  // rounds where the block kernel rounds
+  constexpr int KK = HD / 32, DB = HD / 16;
+  __shared__ __align__(16) float s_o[2][kWaves][16][HD + 4];
+  __shared__ __align__(16) char s_q[QT * KK * 1024];
+  __shared__ float s_m[QT][kWaves][16], s_l[QT][kWaves][16], s_f[QT][kWaves][16], s_L[QT][16];
   touch_kernargs<AttnPrefillArgs>();
   // KV head and query block: workgroups go to the XCDs round-robin by linear id, and a head's query blocks to as few
   // XCDs as give every XCD work (their L2s hold its K/V); the last query blocks, which see most positions, first.
@@ -65,170 +38,193 @@ __global__ void __launch_bounds__(kThreads, 2) attention_prefill_kernel(AttnPref
   const int gh = a.heads_apart, per = a.hkv / gh, parts = kXcds / gh;
   const int kvh = xcd % gh + gh * (slot % per), rank = slot / per * parts + xcd / gh;
   if (rank >= a.qblocks) return;
-  const int qb = a.qblocks - 1 - rank;
+  const int q_first = (a.qblocks - 1 - rank) * 16 * QT;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
-  const int QV = a.R * a.grp, q_first = qb * kQueries, qw = q_first + wave * kQT * 16;
-  const int r_hi = min(a.R - 1, (q_first + kQueries - 1) / a.grp);
+  const int QV = a.R * a.grp, g8 = 8 * (lane / 16);
   const RowInfo first = a.rows[0];
-  const int pos_hi = a.rows[r_hi].pos;
-  const int w_lo = min(a.R - 1, qw / a.grp), w_hi = min(a.R - 1, (qw + kQT * 16 - 1) / a.grp);
-  const int wlo_pos = a.rows[w_lo].pos, whi_pos = a.rows[w_hi].pos;  // the wave's first and last row
-  int qpos[kQT], qrow[kQT], qh[kQT];
-  uint4 qf[kQT][KK];  // lanes past the last query vector hold row 0's (not stored)
-#pragma unroll
-  for (int t = 0; t < kQT; ++t) {
-    const int qv = qw + 16 * t + lane % 16;
-    qrow[t] = qv < QV ? qv / a.grp : 0;
-    qh[t] = kvh * a.grp + (qv < QV ? qv % a.grp : 0);
-    qpos[t] = a.rows[qrow[t]].pos;
-    const uint16_t* Q = a.q + ((int64_t)qrow[t] * a.hq + qh[t]) * HD;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[t][kk] = load16(Q + 32 * kk + 8 * (lane / 16));
+  // fragment f of the queries (tile f / KK, dimensions 32 (f % KK) ..) goes to LDS by wave f % kWaves
+  for (int f = wave; f < QT * KK; f += kWaves) {
+    const int qv = q_first + 16 * (f / KK) + lane % 16;
+    const int r = qv < QV ? qv / a.grp : 0, h = qv < QV ? qv % a.grp : 0;
+    *reinterpret_cast<uint4*>(s_q + f * 1024 + lane * 16) =
+        load16(a.q + ((int64_t)r * a.hq + kvh * a.grp + h) * HD + 32 * (f % KK) + g8);
   }
-  const int kv_end = __builtin_amdgcn_readfirstlane(first.valid ? pos_hi + 1 : 0);
-  const int wave_lo = __builtin_amdgcn_readfirstlane(wlo_pos);
-  const int wave_end = __builtin_amdgcn_readfirstlane(min(whi_pos + 1, kv_end));
-  const int n = (kv_end + 31) / 32;  // steps; (kv_end - 1) / 32 * 32 + 32 <= ld, a multiple of 64
+  // the lane's query's position (-1: none); a tile's first position, the one past its last (a chunk's rows are consecutive)
+  int qpos[QT], lo[QT], end[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int q0 = q_first + 16 * t, qv = q0 + lane % 16;
+    qpos[t] = qv < QV ? first.pos + qv / a.grp : -1;
+    lo[t] = __builtin_amdgcn_readfirstlane(q0 + 15 < QV ? first.pos + q0 / a.grp : -1);
+    end[t] = __builtin_amdgcn_readfirstlane(first.valid && q0 < QV ? first.pos + min(a.R - 1, (q0 + 15) / a.grp) + 1 : 0);
+  }
+  int kv_end = 0;
+#pragma unroll
+  for (int t = 0; t < QT; ++t) kv_end = max(kv_end, end[t]);
   const int64_t head = (int64_t)first.seq * a.hkv + kvh;
-  const int hbytes = a.ld * HD * 2;  // < 2^31: checked on the host
-  char* const K = const_cast<char*>(reinterpret_cast<const char*>(a.kc + head * a.ld * HD));
-  char* const V = const_cast<char*>(reinterpret_cast<const char*>(a.vc + head * a.ld * HD));
-  // the query loads complete before the ring's go out, so that no wait in the loop is for them
-  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  const uint16_t* K = a.kc + head * a.ld * HD + lane * 8;
+  const uint16_t* V = a.vc + head * a.ld * HD + lane * 8;
 
-  // Step t's loads: wave w takes blocks w, w + 4, ... (K first, then V).  Every call issues the same ones, so that
-  // the memory-counter waits count alike; past the last step the descriptors have no range.
-  int slot_b = 0, st = 0;
-  auto issue = [&]() {
-    const int range = st < n ? hbytes : 0;
-    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(K, 0, range, kBufferRsrcWord3);
-    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(V, 0, range, kBufferRsrcWord3);
-    const int ofs = st * (NB / 2) * 1024 + wave * 1024;
+  // A loaded step starts below kv_end <= ld and ld is a multiple of 64, so its blocks lie inside the head's cache.
+  // Entries at positions at or past a tile's end may hold stale values: their scores are masked and their V values
+  // zeroed (P is 0 there, and 0 times a stale non-finite value would not be).
+  uint4 kf[2][KK], vf[DB];
+  auto load_k = [&](int p) {
 #pragma unroll
-    for (int i = 0; i < LQ / 2; ++i) {
-      load_lds16<0>(krs, s_ring + slot_b + (wave + kWaves * i) * 1024, lane * 16, ofs + i * kWaves * 1024);
-      load_lds16<0>(vrs, s_ring + slot_b + (NB / 2 + wave + kWaves * i) * 1024, lane * 16, ofs + i * kWaves * 1024);
-    }
-    slot_b = slot_b + kStage == kRing * kStage ? 0 : slot_b + kStage;
-    ++st;
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) kf[b][kk] = load16(K + (int64_t)(p / 32) * 32 * HD + (b * KK + kk) * 512);
   };
+  auto load_v = [&](int p) {
 #pragma unroll
-  for (int i = 0; i < kRing - 1; ++i) issue();
-
-  f32x4 o[kQT][DB];
-  float m[kQT], l[kQT];  // running maximum (scaled, base 2) and this lane's part of the sum
+    for (int db = 0; db < DB; ++db) vf[db] = load16(V + (int64_t)(p / 32) * 32 * HD + db * 512);
+  };
+  f32x4 o[QT][DB];
+  float m[QT], l[QT];  // running maximum, this lane's part of the sum
 #pragma unroll
-  for (int t = 0; t < kQT; ++t) {
+  for (int t = 0; t < QT; ++t) {
     m[t] = -INFINITY;
     l[t] = 0.f;
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[t][db] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const float c = a.scale * 1.44269504088896340736f;
-  const int g8 = 8 * (lane / 16);
-  const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(s_ring) + lane * 16;
-  uint32_t so = 0;
+  constexpr int kStride = 32 * kWaves;
+  const int p_last = kv_end > 0 ? (kv_end - 1) / 32 * 32 : 0;
+  const bool any = kv_end > 32 * wave;
+  if (any) {
+    load_k(32 * wave);
+    load_v(32 * wave);
+  }
+  __syncthreads();  // the queries are in LDS
 #pragma unroll 1
-  for (int s = 0; s < n; ++s) {
-    __builtin_amdgcn_s_waitcnt(wait_vmcnt((kRing - 2) * LQ));  // this wave's loads of step s have landed
-    phase_barrier();  // everyone's have, and the slot of step s - 1 has been read by every wave
-    issue();
-    u32x4 f[NB];
-    read_step<HD>(f, ring + so);
-    so = so + kStage == kRing * kStage ? 0 : so + kStage;
-    const int p = 32 * s;
-    if (p >= wave_end) continue;  // past all of this wave's queries
-    f32x4 sc[kQT][2];
+  for (int p = 32 * wave; p < kv_end; p += kStride) {
+    f32x4 sacc[QT][2];
 #pragma unroll
-    for (int t = 0; t < kQT; ++t)
+    for (int t = 0; t < QT; ++t) {
+      sacc[t][0] = sacc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (p < end[t]) {
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        sc[t][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kk = 0; kk < KK; ++kk) {
+          const bf16x8 q = *reinterpret_cast<const bf16x8*>(s_q + (t * KK + kk) * 1024 + lane * 16);
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-          sc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[b * KK + kk]),
-                                                             __builtin_bit_cast(bf16x8, qf[t][kk]), sc[t][b], 0, 0, 0);
+          for (int b = 0; b < 2; ++b)
+            sacc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[b][kk]), q, sacc[t][b], 0, 0, 0);
+        }
       }
-    // sc[t][b][i]: position p + g8 + 4 b + i of the lane's query
-    if (p + 31 > wave_lo) {  // the step reaches past the wave's first row's position
-#pragma unroll
-      for (int t = 0; t < kQT; ++t)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (p + g8 + 4 * b + i > qpos[t]) sc[t][b][i] = -INFINITY;
-      // entries past the wave's last position may hold stale values, and 0 times a non-finite one is not 0
-      const int nv = wave_end - (p + g8);
-      uint32_t mask[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) mask[i] = (2 * i < nv ? 0xFFFFu : 0u) | (2 * i + 1 < nv ? 0xFFFF0000u : 0u);
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) f[2 * KK + db][i] &= mask[i];
     }
-    uint4 pf[kQT];
+    load_k(min(p + kStride, p_last));
+    __builtin_amdgcn_sched_barrier(0);
+    uint4 pf[QT];
 #pragma unroll
-    for (int t = 0; t < kQT; ++t) {
-      float mx = fmaxf(fmaxf(fmaxf(sc[t][0][0], sc[t][0][1]), fmaxf(sc[t][0][2], sc[t][0][3])),
-                       fmaxf(fmaxf(sc[t][1][0], sc[t][1][1]), fmaxf(sc[t][1][2], sc[t][1][3])));
-      mx = xor16_op(mx, [](float x, float y) { return fmaxf(x, y); });
-      mx = xor32_op(mx, [](float x, float y) { return fmaxf(x, y); }) * c;
-      if (__any(mx > m[t])) {
-        const float mnew = fmaxf(m[t], mx);
-        const float alpha = m[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[t] - mnew);
-        m[t] = mnew;
-        l[t] *= alpha;
+    for (int t = 0; t < QT; ++t) {
+      pf[t] = make_uint4(0, 0, 0, 0);
+      if (p >= end[t]) continue;
+      // sacc[t][b][i]: position p + g8 + 4 b + i, query column lane % 16
+      float sv[8];
 #pragma unroll
-        for (int db = 0; db < DB; ++db) o[t][db] *= alpha;
+      for (int i = 0; i < 8; ++i) sv[i] = sacc[t][i / 4][i % 4] * a.scale;
+      if (p + 31 > lo[t]) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sv[i] = p + g8 + i <= qpos[t] ? sv[i] : -INFINITY;
       }
-      const float mm = m[t] == -INFINITY ? 0.f : m[t];  // (a query with no position so far: every term is 2^-inf)
+      float mloc = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) mloc = fmaxf(mloc, sv[i]);
+      mloc = xor16_op(mloc, [](float x, float y) { return fmaxf(x, y); });
+      mloc = xor32_op(mloc, [](float x, float y) { return fmaxf(x, y); });
+      const float mnew = fmaxf(m[t], mloc);
+      float lsum = 0.f;
       float e[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[t][i / 4][i % 4], c, -mm));
-      l[t] += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+      for (int i = 0; i < 8; ++i) {
+        e[i] = sv[i] == -INFINITY ? 0.f : __expf(sv[i] - mnew);
+        lsum += e[i];
+      }
       pf[t] = make_uint4(pack_bf16x2(e[0], e[1]), pack_bf16x2(e[2], e[3]), pack_bf16x2(e[4], e[5]), pack_bf16x2(e[6], e[7]));
+      if (__any(mnew != m[t])) {
+        const float alpha = m[t] == -INFINITY ? 0.f : __expf(m[t] - mnew);
+        l[t] = __builtin_fmaf(l[t], alpha, lsum);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[t][db] *= alpha;
+        m[t] = mnew;
+      } else {
+        l[t] += lsum;
+      }
     }
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      if (p >= end[t]) continue;
+      if (p + 32 > end[t]) {
+        const int nv = end[t] - (p + g8);  // valid positions of the lane's 8 (may be <= 0 or >= 8)
+        uint32_t mask[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mask[i] = (2 * i < nv ? 0xFFFFu : 0u) | (2 * i + 1 < nv ? 0xFFFF0000u : 0u);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          const uint4 v = make_uint4(vf[db].x & mask[0], vf[db].y & mask[1], vf[db].z & mask[2], vf[db].w & mask[3]);
+          o[t][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pf[t]),
+                                                             o[t][db], 0, 0, 0);
+        }
+      } else {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          o[t][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[db]),
+                                                             __builtin_bit_cast(bf16x8, pf[t]), o[t][db], 0, 0, 0);
+      }
+    }
+    load_v(min(p + kStride, p_last));
+  }
+  // the waves' partial (max, sum, O) in wave order; O two tiles at a time through LDS
+  auto publish = [&](int t) {
 #pragma unroll
     for (int db = 0; db < DB; ++db)
+      *reinterpret_cast<f32x4*>(&s_o[t % 2][wave][lane % 16][16 * db + 4 * (lane / 16)]) = o[t][db];
+  };
 #pragma unroll
-      for (int t = 0; t < kQT; ++t)
-        o[t][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[2 * KK + db]),
-                                                           __builtin_bit_cast(bf16x8, pf[t]), o[t][db], 0, 0, 0);
-  }
-  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // the loads past the end (no memory access) before the block may end
-  // o[t][db][i]: dimension 16 db + 4 (lane / 16) + i of query lane % 16
-#pragma unroll
-  for (int t = 0; t < kQT; ++t) {
-    float L = xor16_op(l[t], [](float x, float y) { return x + y; });
-    L = xor32_op(L, [](float x, float y) { return x + y; });
-    const float inv = 1.f / L;
-    if (qw + 16 * t + lane % 16 < QV) {
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-        *reinterpret_cast<uint2*>(a.out + xfrag_index<uint16_t>(qrow[t], qh[t] * HD + 16 * db + 4 * (lane / 16), a.hq * HD / 32)) =
-            L > 0.f ? make_uint2(pack_bf16x2(o[t][db][0] * inv, o[t][db][1] * inv),
-                                 pack_bf16x2(o[t][db][2] * inv, o[t][db][3] * inv))
-                    : make_uint2(0, 0);
+  for (int t = 0; t < QT; ++t) {
+    float ltot = xor16_op(l[t], [](float x, float y) { return x + y; });
+    ltot = xor32_op(ltot, [](float x, float y) { return x + y; });
+    if (lane < 16) {
+      s_m[t][wave][lane] = m[t];
+      s_l[t][wave][lane] = ltot;
     }
+  }
+#pragma unroll
+  for (int t0 = 0; t0 < QT; t0 += 2) {
+    if (t0 > 0) __syncthreads();
+#pragma unroll
+    for (int t = t0; t < min(QT, t0 + 2); ++t) publish(t);
+    __syncthreads();
+    if (t0 == 0) {
+      const int i = threadIdx.x;
+      if (i < 16 * QT) attn_factors(s_m[i / 16], s_l[i / 16], s_f[i / 16], s_L[i / 16], i % 16);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int t = t0; t < min(QT, t0 + 2); ++t)
+      attn_combine<HD>(s_o[t % 2], s_f[t], s_L[t], [&](int q, int dim, const float* y) {
+        const int qv = q_first + 16 * t + q;
+        if (qv < QV)
+          *reinterpret_cast<uint2*>(a.out + xfrag_index<uint16_t>(qv / a.grp, (kvh * a.grp + qv % a.grp) * HD + dim,
+                                                                  a.hq * HD / 32)) =
+              make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+      });
   }
 }
 
 }  // namespace
 
 int launch_attention_prefill(AttnPrefillArgs a, int head_dim, hipStream_t st) {
-  if ((int64_t)a.ld * head_dim * 2 >= (int64_t(1) << 31))
-    return fail(SDD_EUNSUPPORTED, "a cache of %d positions exceeds the 32-bit buffer offsets", a.ld);
-  a.qblocks = (int)ceil_div((int64_t)a.R * a.grp, kQueries);
+  constexpr int QT = kAttnPrefillQueries / 16;
+  a.qblocks = (int)ceil_div((int64_t)a.R * a.grp, 16 * QT);
   a.heads_apart = kXcds;  // the largest power of two up to 8 that divides the KV heads
   while (a.hkv % a.heads_apart) a.heads_apart /= 2;
   const int per = a.hkv / a.heads_apart, parts = kXcds / a.heads_apart;
   const dim3 grid(kXcds * per * (int)ceil_div(a.qblocks, parts));
   if (head_dim == 128)
-    hipLaunchKernelGGL(attention_prefill_kernel<128>, grid, dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((attention_prefill_kernel<128, QT>), grid, dim3(kThreads), 0, st, a);
   else
-    hipLaunchKernelGGL(attention_prefill_kernel<64>, grid, dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((attention_prefill_kernel<64, QT>), grid, dim3(kThreads), 0, st, a);
   return check_launch("attention_prefill_kernel");
 }
 

@@ -841,8 +841,6 @@ __global__ void __launch_bounds__(256) attention_kernel(AttnArgs a) {
 // every operand load is a contiguous 1 KB block.  Each wave keeps two steps of
 // K/V loads in flight.  The softmax is online within a wave; the waves' partial
 // (max, sum, O) are combined through LDS in wave order.
-constexpr int kAttnWaves = 8;
-
 struct AttnMfmaArgs {
   const uint16_t* q;   // [rows][hq][HD]
   const uint16_t* kc;  // layer base, per (seq, hkv) ld x HD elements, fragment-major
@@ -1045,45 +1043,16 @@ __global__ void __launch_bounds__(kAttnWaves * 64) attention_mfma_kernel(AttnMfm
     s_l[wave][lane] = ltot;
   }
   __syncthreads();
-  // per query: the common max, each wave's rescale factor and the total sum,
-  // all accumulated in wave order
-  if (threadIdx.x < 16) {
-    const int q = threadIdx.x;
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) M = fmaxf(M, s_m[w][q]);
-    float L = 0.f;
-#pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) {
-      const float ms = s_m[w][q];
-      const float f = (M == -INFINITY || ms == -INFINITY) ? 0.f : __expf(ms - M);
-      s_f[w][q] = f;
-      L += s_l[w][q] * f;
-    }
-    s_L[q] = L;
-  }
+  if (threadIdx.x < 16) attn_factors(s_m, s_l, s_f, s_L, threadIdx.x);
   __syncthreads();
-  // four consecutive dimensions per thread (one 8-byte store into the fragment-major rows)
-  for (int e = threadIdx.x; e < 16 * HD / 4; e += kAttnWaves * 64) {
-    const int q = e / (HD / 4), dim = 4 * (e % (HD / 4));
+  // (one 8-byte store of four dimensions into the fragment-major rows)
+  attn_combine<HD>(s_o, s_f, s_L, [&](int q, int dim, const float* y) {
     const int qq = qb * 16 + q;
-    if (qq >= QV) continue;
-    f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[w][q][dim]);
-      const float f = s_f[w][q];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) O[i] += v[i] * f;
-    }
-    const float L = s_L[q];
-    const int rr = qq / a.grp, hq2 = kvh * a.grp + qq % a.grp;
-    float y[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] = L > 0.f ? O[i] / L : 0.f;
-    *reinterpret_cast<uint2*>(a.out + xfrag_index<uint16_t>(blk * a.R + rr, hq2 * HD + dim, a.hq * HD / 32)) =
-        make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
-  }
+    if (qq < QV)
+      *reinterpret_cast<uint2*>(a.out + xfrag_index<uint16_t>(blk * a.R + qq / a.grp, (kvh * a.grp + qq % a.grp) * HD + dim,
+                                                              a.hq * HD / 32)) =
+          make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -1286,9 +1255,9 @@ static WsLayout rows_layout(const sdd_model* m, int max_rows) {
   L.x = take((size_t)mp * d * 4);
   L.xa = take((size_t)mp * d * es);
   L.ss_part = take((size_t)ceil_div(d, 16) * mp * 4);
-  L.q = take((size_t)mp * hq * es);
-  L.ao = take((size_t)mp * hq * es);
   L.ffh = take((size_t)mp * c.d_ff * es);
+  L.q = take((size_t)mp * hq * es);   // q and ao before the partial tiles: the down projection's (the most of a layer) may
+  L.ao = take((size_t)mp * hq * es);  // take their room too, which nothing reads then
   L.total = off;
   return L;
 }
@@ -1403,6 +1372,7 @@ static int run_gemm(CallCtx& cx, int epi, unsigned prof, size_t w_off, int64_t N
   if ((int64_t)(M + 64) * K * m->es >= (int64_t(1) << 31))
     return fail(SDD_EUNSUPPORTED, "activations of %d rows x %d exceed the 32-bit buffer offsets", M, K);
   if (many_rows(m, M, ng)) {
+    if (prof == PROF_GEMM_DOWN) a.part = reinterpret_cast<float*>(cx.ws + cx.L.q);  // (plan_forward)
     a.Wn = nullptr;
     a.M = M;
     a.ng = ng;
@@ -1459,31 +1429,26 @@ struct ForwardPlans {
   TilePlan qkv{}, o{}, gu{}, down{}, lm{};
   double layer_us() const { return qkv.us + o.us + gu.us + down.us; }
 };
-static ForwardPlans plan_forward(const sdd_model* m, int M, size_t part_bytes, bool lm) {
+static ForwardPlans plan_forward(const sdd_model* m, int M, const WsLayout& L, bool lm) {
   ForwardPlans p;
-  auto plan = [&](const MatPlan& mp) { return many_rows(m, M, mp.ng) ? plan_tiles(mp, M, m->n_cu, part_bytes, gemm_counter_count(m)) : TilePlan{}; };
-  p.qkv = plan(m->plan_qkv);
-  p.o = plan(m->plan_o);
-  p.gu = plan(m->plan_gu);
-  p.down = plan(m->plan_down);
-  if (lm) p.lm = plan(m->plan_lm);
+  auto plan = [&](const MatPlan& mp, bool pairs, size_t from) {
+    return many_rows(m, M, mp.ng) ? plan_tiles(mp, pairs, M, m->n_cu, L.part + L.part_bytes - from, gemm_counter_count(m)) : TilePlan{};
+  };
+  p.qkv = plan(m->plan_qkv, false, L.part);
+  p.o = plan(m->plan_o, false, L.part);
+  p.gu = plan(m->plan_gu, true, L.part);
+  p.down = plan(m->plan_down, false, L.q);
+  if (lm) p.lm = plan(m->plan_lm, true, L.part);
   return p;
 }
 
-// Whether one layer's attention of a prefill chunk of R rows that ends at position `npos` takes the prefill kernel.
-// That kernel walks the positions in sequence, about 7 us + 0.8 us per 32-position step while it does not fill the
-// chip; the block kernel splits them over its waves, about 13 us + 0.83 us per step and 16000 (row, query head)
-// pairs.  Measured, prefill against block kernel (us per launch, Qwen3-32B / Qwen2.5-7B heads): 66 rows at position 0
-// 10 / 10 against 17 / 15, 1024 rows 44 / 37 against 153 / 131, 4096 rows 344 / 168 against 1072 / 913, 1000 rows
-// of a 4000-token prompt 100 / 86 against 266 / 294; 95 rows of it 60 against 36, hence the line.
-static bool prefill_attention(const sdd_model* m, int R, int npos) {
-  const double steps = ceil_div(npos, 32);
-  return m->es == 2 && R > kMaxBlockRows && 0.8 * steps <= 6.0 + steps * R * m->cfg.n_q_heads / 19200.0;
-}
+// Whether the attention of a prefill chunk of R rows takes the prefill kernel, which gives the block kernel's bits and is
+// faster from 65 rows on (attn_prefill.hip; 66 rows 12 us against 17).
+static bool prefill_attention(const sdd_model* m, int R) { return m->es == 2 && R > kMaxPassRows; }
 
-// Forward of nb blocks of R rows whose RowInfo/x/xa/sum of squares were written by embed_kernel.  prefill_end: the
-// position after a prefill chunk's last row (one block), 0 for a verify call.
-static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argmax, int prefill_end = 0) {
+// Forward of nb blocks of R rows whose RowInfo/x/xa/sum of squares were written by embed_kernel (prefill: one block,
+// a chunk of a prompt).
+static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argmax, bool prefill = false) {
   const int M = nb * R;
   sdd_model* m = cx.m;
   sdd_kv* kv = cx.kv;
@@ -1495,7 +1460,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
   char* xa = ws + L.xa;
   float* ss = reinterpret_cast<float*>(ws + L.ss_part);
   // column groups of the RMSNorm statistic of the current residual stream
-  const ForwardPlans tp = plan_forward(m, M, L.part_bytes, logits != nullptr);
+  const ForwardPlans tp = plan_forward(m, M, L, logits != nullptr);
   const int g_resid_o = (int)(d / 16 / m->ng_o), g_resid_down = (int)(d / 16 / m->ng_down);
   int ss_groups = 1;  // from embed_kernel
   int rc;
@@ -1522,7 +1487,7 @@ static int forward_rows(CallCtx& cx, int nb, int R, float* logits, int32_t* argm
       if ((rc = run_gemm(cx, EPI_QKV, PROF_GEMM_QKV, Ly.qkv, hq + 2 * hk, (int)d, xa, a, M, m->ng_qkv, tp.qkv, &nx))) return rc;
     }
     // attention
-    if (prefill_end > 0 && prefill_attention(m, R, prefill_end)) {
+    if (prefill && prefill_attention(m, R)) {
       AttnPrefillArgs a{};
       a.q = reinterpret_cast<const uint16_t*>(ws + L.q);
       a.kc = reinterpret_cast<const uint16_t*>(kv->k + (size_t)l * kv->layer_stride);
@@ -1774,36 +1739,60 @@ static int make_ctx(CallCtx& cx, sdd_model* m, sdd_kv* kv, void* ws, size_t ws_b
   return SDD_OK;
 }
 
-// Rows per prefill chunk of n rows in a workspace of `bytes`.  fp32 models: the largest power of two up to 256
-// whose verify layout fits.  bf16: larger chunks amortise the weights and fill the matrix cores, so the prompt is cut
-// into equal chunks, as few as the workspace holds (without argmax records, everything past the rows' buffers
-// being room for partial tiles), or up to three more where the GEMMs' estimated time comes out lower.
-static int prefill_chunk(const sdd_model* m, int n, size_t bytes) {
-  if (m->es != 2) {
-    for (int r : {256, 128, 64, 32})
-      if (ws_layout(m, r).total <= bytes) return r;
-    return 16;
-  }
+// How n rows of a prompt are cut into chunks in a workspace of `bytes`: the first `main` rows into k chunks of whole
+// 16-row tiles, sizes as equal as that allows, the rest into chunks of at most `rest` rows.
+struct PrefillPlan {
+  int main, k, rest;
+  int layout;  // rows of the workspace's layout
+  int begin(int i) const { return i < k ? (int)(16 * (ceil_div(main, 16) * i / k)) : main; }
+};
+
+// A row is summed in one of two orders, that of the kernels for up to 64 rows or that of the many-row kernel, and which
+// one is fixed by its position and the workspace: rows go in passes of the largest power of two up to 256 whose verify
+// layout fits, and a pass of at most 64 rows (a small workspace's, or the last one) takes the first order.  fp32 models
+// run those passes.  bf16: larger chunks amortise the weights and fill the matrix cores, and their rows' results do not
+// depend on the chunk, so the rows of the passes over 64 rows are cut into as few chunks as the workspace holds (without
+// argmax records, everything past the rows' buffers being room for partial tiles), or up to three more where the GEMMs'
+// estimated time comes out lower.
+static PrefillPlan plan_prefill(const sdd_model* m, int n, size_t bytes) {
+  int pass = 16;
+  for (int r : {256, 128, 64, 32})
+    if (ws_layout(m, r).total <= bytes) {
+      pass = r;
+      break;
+    }
+  if (m->es != 2) return PrefillPlan{0, 0, pass, pass};
   auto fits = [&](int r) { return prefill_layout(m, r, bytes).total <= bytes; };
-  int lo = 16, hi = std::max(16, std::min((int)align_up((size_t)std::max(n, 1), 16), kPrefillMaxRows));
-  while (lo < hi) {  // the largest multiple of 16 that fits
-    const int mid = (lo + hi + 16) / 32 * 16;
-    if (fits(mid)) lo = mid; else hi = mid - 16;
+  if (pass <= kMaxPassRows) {
+    int r = kMaxPassRows;
+    while (r > 16 && !fits(r)) r -= 16;
+    return PrefillPlan{0, 0, r, r};
   }
-  if (n <= lo && lo <= kMaxPassRows) return lo;
-  int best = lo;
+  PrefillPlan p{n, 1, kMaxPassRows, kMaxPassRows};
+  if (n % pass <= kMaxPassRows) p.main = n - n % pass;
+  if (p.main == 0) return p;
+  // the largest chunk that fits, in 16-row tiles (at least pass / 16, so 8).  Every chunk holds more than 64 rows, 5 tiles
+  // or more of which the last may be short by 15 rows: where two chunks are needed main is at least pass + 65, so that 13
+  // tiles or more are cut in two, and k chunks are needed only for more than 8 (k - 1) tiles.
+  const int tiles = (int)ceil_div(p.main, 16);
+  int lo = pass / 16, hi = std::max(lo, std::min(tiles, kPrefillMaxRows / 16));
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (fits(16 * mid)) lo = mid; else hi = mid - 1;
+  }
   double best_us = 1e30;
-  const int k0 = (int)ceil_div(n, lo);
+  const int k0 = (int)ceil_div(tiles, lo);
   for (int k = k0; k < k0 + 4; ++k) {
-    const int r = (int)align_up((size_t)ceil_div(n, k), 16);
-    if (r <= kMaxPassRows && k > k0) break;
-    const double us = k * plan_forward(m, r, prefill_layout(m, r, bytes).part_bytes, false).layer_us();
+    if (k > k0 && tiles / k < 6) break;
+    const int r = 16 * (int)ceil_div(tiles, k);
+    const double us = k * plan_forward(m, r, prefill_layout(m, r, bytes), false).layer_us();
     if (us < best_us) {
       best_us = us;
-      best = r;
+      p.k = k;
+      p.layout = r;
     }
   }
-  return best;
+  return p;
 }
 
 extern "C" int sdd_kv_prefill(sdd_model* m, sdd_kv* kv, int seq, const int32_t* tokens, int n, void* ws,
@@ -1814,13 +1803,13 @@ extern "C" int sdd_kv_prefill(sdd_model* m, sdd_kv* kv, int seq, const int32_t* 
   if (n - 1 > kv->max_len) return fail(SDD_ECAPACITY, "prompt of %d tokens exceeds max_len %d", n, kv->max_len);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (ws_layout(m, 16).total > ws_bytes) return fail(SDD_ECAPACITY, "workspace too small for prefill");
-  const int chunk = prefill_chunk(m, n - 1, ws_bytes);
-  for (int c0 = 0; c0 < n - 1; c0 += chunk) {
-    const int rows = std::min(chunk, n - 1 - c0);
+  const PrefillPlan plan = plan_prefill(m, n - 1, ws_bytes);
+  for (int i = 0, c0 = 0; c0 < n - 1; ++i) {
+    const int rows = c0 < plan.main ? plan.begin(i + 1) - c0 : std::min(plan.rest, n - 1 - c0);
     CallCtx cx;
     int rc = make_ctx(cx, m, kv, ws, ws_bytes, 16, st);
     if (rc) return rc;
-    cx.L = prefill_layout(m, chunk, ws_bytes);
+    cx.L = prefill_layout(m, plan.layout, ws_bytes);
     EmbedArgs e{};
     e.prefill = 1;
     e.seq = seq;
@@ -1828,7 +1817,8 @@ extern "C" int sdd_kv_prefill(sdd_model* m, sdd_kv* kv, int seq, const int32_t* 
     e.tokens = tokens + c0;
     e.R = rows;
     if ((rc = launch_embed(cx, e, rows))) return rc;
-    if ((rc = forward_rows(cx, 1, rows, nullptr, nullptr, c0 + rows))) return rc;
+    if ((rc = forward_rows(cx, 1, rows, nullptr, nullptr, true))) return rc;
+    c0 += rows;
   }
   hipLaunchKernelGGL(prefill_finish_kernel, dim3(1), dim3(64), 0, st, kv->len, kv->pending, kv->err, seq, n, tokens,
                      m->cfg.vocab);

@@ -33,7 +33,7 @@ struct GemmArgs {
   int n_wg;
   int segc;       // virtual units per column group of the plan (cost-balanced shares; 0: equal)
   int share;      // longest share (units): the stored matrix holds share x n_wg slots
-  float* part;    // partial tiles [n_wg][2][M][NG*16]
+  float* part;    // partial tiles [n_wg][2][M][NG*16] (many-row kernel: partial or running sums by place)
   int32_t* err;   // the KV cache's sticky error word (bit3: a workgroup's internal hand-off gave up)
   int* cnt;       // arrival counter per column group (group g at cnt[g * kCntStride])
   const RowInfo* rows;
@@ -69,9 +69,10 @@ struct GemmArgs {
   // only contributed a partial loads into L2 before it ends
   const char* Wn;
   int KTn, Gn, ngn, nwg_n, cn;
-  // many-row kernel: column tiles per column group, column blocks (the first ncb1 not split), row blocks, k-ranges per
-  // split tile
-  int ng, ncb, ncb1, nrb, ksplit;
+  // many-row kernel: column tiles per column group; this launch's column blocks from cb0, row blocks, contributors per
+  // tile, K segments (SumPlan), partial sums per tile, places of running sums per row block
+  int ng, cb0, ncb, nrb, ksplit;
+  int sg, sG, sn, sc, nslot, nch, compact;
 };
 
 template <typename T>
@@ -566,18 +567,154 @@ __device__ inline void phase_barrier() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
-// Many-row GEMM (tiles.hip): bf16 weights, column groups of 8 or 4 tiles, rows [0, a.M) in one launch; fused
-// epilogue `epi`.  A plan fixes the tile (128 wc columns x 128 rtw / wc rows per workgroup), the number of column and
-// row blocks and what is split over k.
+// The order of a row's sums over K in the many-row kernel.  The K x column-group units of a matrix, G groups of `tiles`
+// column tiles each, are shared out among n owners (unit_start with c virtual units); inside a group every share is one
+// segment: the k-steps of a segment are added one after another, from zero, and the segments' sums in order.  It is a
+// property of the matrix alone: a row's result does not depend on the rows, tiles and splits of the launch it is in.
+// The groups and shares are those of the storage plan, or equal shares of pairs of 8-tile groups (gate/up and the LM
+// head, whose tiles are mostly one segment).
+struct SumPlan {
+  int tiles, G, n, c;
+  int nseg;      // segments per group (uniform), or a bound
+  bool uniform;  // every group has the same segments
+};
+SumPlan sum_plan(const MatPlan& mp, bool pairs);
+// Many-row GEMM (tiles.hip): bf16 weights, column groups of 8 or 4 tiles, rows [0, a.M); fused epilogue `epi`.  A plan
+// fixes the tile (128 wc columns x 128 rtw / wc rows per workgroup), the number of column and row blocks and the
+// workgroups that share a tile's segments.
 struct TilePlan {
   int wc, rtw;            // wave columns (1 or 2) of the workgroup's 8 waves, row tiles per wave
   int ncb, nrb;           // column blocks, row blocks
-  int ncb1, ksplit;       // column blocks that are not split, k-ranges per tile of the others
+  int per, ksplit;        // column blocks per launch, workgroups per tile
+  int slots;              // partial sums per split tile
+  bool compact;           // one running sum per segment boundary of the matrix (else one per 64 columns)
+  SumPlan sums;
   double us;              // estimated time
 };
-// Best plan for M rows of a matrix of plan `mp` on n_cu compute units, with `part_bytes` for split partials and
-// arrival counters for max_split tiles.
-TilePlan plan_tiles(const MatPlan& mp, int M, int n_cu, size_t part_bytes, int64_t max_split);
+// Best plan for M rows of a matrix of plan `mp` (pairs: gate/up or LM head) on n_cu compute units, with `part_bytes` for
+// partial and running sums and arrival counters for max_split tiles.
+TilePlan plan_tiles(const MatPlan& mp, bool pairs, int M, int n_cu, size_t part_bytes, int64_t max_split);
+// Index arithmetic of a many-row launch (host and device: the tests replay it on the CPU).
+// Launch fields of column blocks from cb0 on.
+inline void tile_launch(GemmArgs& a, const TilePlan& p, int cb0) {
+  a.cb0 = cb0;
+  a.ncb = std::min(p.per, p.ncb - cb0);
+  a.nrb = p.nrb;
+  a.ksplit = p.ksplit;
+  a.sg = p.sums.tiles;
+  a.sG = p.sums.G;
+  a.sn = p.sums.n;
+  a.sc = p.sums.c;
+  a.nslot = p.slots;
+  a.nch = a.ncb * 2 * p.wc;
+  a.compact = p.compact;
+}
+inline int tile_grid(const GemmArgs& a) { return kXcds * (int)ceil_div((int64_t)a.ncb * a.ksplit, kXcds) * a.nrb; }
+// A workgroup's item: column block (of the launch and of the matrix), row block, contributor; cbl < 0: none.
+// One XCD's workgroups are 8 apart; the row blocks of a column block run there next to each other.
+struct TileItem {
+  int cbl, cb, rb, sp;
+};
+__host__ __device__ inline TileItem tile_item(const GemmArgs& a, int block, int S) {
+  const int slot = block / kXcds, cs = block % kXcds + kXcds * (slot / a.nrb);
+  return cs < a.ncb * S ? TileItem{cs / S, a.cb0 + cs / S, slot % a.nrb, cs % S} : TileItem{-1, 0, 0, 0};
+}
+// First unit of the sum group of column tile ct (past the matrix: of the last group).
+__host__ __device__ inline uint32_t sum_base(const GemmArgs& a, int ct) {
+  const int g = ct / a.sg;
+  return (uint32_t)(g < a.sG ? g : a.sG - 1) * (uint32_t)a.KT;
+}
+__host__ __device__ inline int sum_owner(const GemmArgs& a, uint32_t u) {
+  return unit_owner(u, (uint32_t)a.KT, (uint32_t)a.sG, (uint32_t)a.sc, (uint32_t)a.sn);
+}
+// k-step (of the group with first unit `base`) at which owner o's share starts
+__host__ __device__ inline int sum_start(const GemmArgs& a, uint32_t base, int o) {
+  return (int)(unit_start((uint32_t)o, (uint32_t)a.KT, (uint32_t)a.sG, (uint32_t)a.sc, (uint32_t)a.sn) - base);
+}
+// Contributor sp's part of a split tile at column tile ct: segments from seg0, k-steps [kb, ke).  The first contributor
+// adds its n0 segments up, so a tile's partial sums take nseg - n0 + 1 slots (part_slot).
+struct TileRange {
+  int kb, ke, own0, nseg, seg0, n0, E;  // own0: owner of the group's first segment; E: contributors (sp >= E has none)
+};
+__host__ __device__ inline TileRange tile_range(const GemmArgs& a, int ct, int sp) {
+  TileRange r{0, a.KT, 0, 1, 0, 1, 1};
+  const uint32_t u0 = sum_base(a, ct);
+  r.own0 = sum_owner(a, u0);
+  r.nseg = sum_owner(a, u0 + (uint32_t)a.KT - 1) - r.own0 + 1;
+  r.E = r.nseg < a.ksplit ? r.nseg : a.ksplit;
+  r.n0 = (r.nseg + r.E - 1) / r.E;
+  if (sp >= r.E) return r;
+  const int s1 = (r.nseg * (sp + 1) + r.E - 1) / r.E;
+  r.seg0 = (r.nseg * sp + r.E - 1) / r.E;
+  if (r.seg0 > 0) r.kb = sum_start(a, u0, r.own0 + r.seg0);
+  if (s1 < r.nseg) r.ke = sum_start(a, u0, r.own0 + s1);
+  return r;
+}
+__host__ __device__ inline int part_slot(const TileRange& r, int seg) { return seg < r.n0 ? 0 : seg - r.n0 + 1; }
+// Byte offset of the running sums of four column tiles from ct (a multiple of four) of row block rb, RT row tiles of 4
+// KiB: one place per 64 columns and row block, or per boundary where a group has at most one (own: the owner before it).
+__host__ __device__ inline int chain_place(const GemmArgs& a, int rb, int ct, int own, int CG, int RT) {
+  const int q = a.sg / 4;
+  return (a.compact ? (rb * a.sn + own) * q + ct / 4 % q : rb * a.nch + ct / 4 - a.cb0 * CG / 4) * RT * 4096;
+}
+// Byte offset of partial sums `slot` of row tile rt and wave column wcol (8 KiB), for tile rb * ncb + cbl.
+__host__ __device__ inline int part_place(const GemmArgs& a, int tile, int slot, int rt, int wcol, int RT, int WC) {
+  return (((tile * a.nslot + slot) * RT + rt) * WC + wcol) * 8192;
+}
+// Where the matrix's streaming plan stores k-step k of column group g: unit g KT + k of owner o, at slot
+// (g KT + k - start(o)) n_wg + o.  Follows one group's owners as k rises.
+struct TileTrk {
+  int g, o, kend, base;  // group, owner, first k-step past its share, slot of k-step 0
+};
+__host__ __device__ inline void trk_set(const GemmArgs& a, TileTrk& t, int o) {
+  const uint32_t KT = (uint32_t)a.KT, u = (uint32_t)t.g * KT;
+  const uint32_t us = unit_start((uint32_t)o, KT, (uint32_t)a.G, (uint32_t)a.segc, (uint32_t)a.n_wg);
+  const uint32_t ue = unit_start((uint32_t)o + 1, KT, (uint32_t)a.G, (uint32_t)a.segc, (uint32_t)a.n_wg);
+  t.o = o;
+  t.kend = (int)(ue - u);
+  t.base = ((int)u - (int)us) * a.n_wg + o;
+}
+
+// ---- attention (bf16) -----------------------------------------------------------------------------------
+constexpr int kAttnWaves = 8;  // waves of a workgroup; wave w takes the 32-position steps w, w + kAttnWaves, ...
+
+// Combining the waves' partial (max, sum, O) of 16 queries, published to LDS, in wave order.  First, for query q: the common
+// max, each wave's rescale factor and the total sum.
+__device__ inline void attn_factors(const float (*s_m)[16], const float (*s_l)[16], float (*s_f)[16], float* s_L, int q) {
+  float M = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < kAttnWaves; ++w) M = fmaxf(M, s_m[w][q]);
+  float L = 0.f;
+#pragma unroll
+  for (int w = 0; w < kAttnWaves; ++w) {
+    const float ms = s_m[w][q];
+    const float f = (M == -INFINITY || ms == -INFINITY) ? 0.f : __expf(ms - M);
+    s_f[w][q] = f;
+    L += s_l[w][q] * f;
+  }
+  s_L[q] = L;
+}
+// Then (a barrier later) the outputs: put(query, dim, y) receives four consecutive dimensions.
+template <int HD, typename Put>
+__device__ inline void attn_combine(const float (*s_o)[16][HD + 4], const float (*s_f)[16], const float* s_L, Put put) {
+  for (int e = threadIdx.x; e < 16 * HD / 4; e += kAttnWaves * kWave) {
+    const int q = e / (HD / 4), dim = 4 * (e % (HD / 4));
+    f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kAttnWaves; ++w) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[w][q][dim]);
+      const float f = s_f[w][q];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) O[i] += v[i] * f;
+    }
+    const float L = s_L[q];
+    float y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = L > 0.f ? O[i] / L : 0.f;
+    put(q, dim, y);
+  }
+}
+
 // Attention of a prefill chunk (attn_prefill.hip, bf16): R rows of one sequence, rows[0, R), over its cache.
 struct AttnPrefillArgs {
   const uint16_t* q;   // [rows][hq][head_dim]
@@ -589,6 +726,7 @@ struct AttnPrefillArgs {
   float scale;
   int qblocks, heads_apart;  // set by the launch
 };
+constexpr int kAttnPrefillQueries = 48;  // query vectors per workgroup
 int launch_attention_prefill(AttnPrefillArgs a, int head_dim, hipStream_t st);
 int launch_gemm_tiles(const TilePlan& p, int epi, GemmArgs a, hipStream_t st);
 

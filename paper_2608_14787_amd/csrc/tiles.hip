@@ -13,16 +13,22 @@
 //  - the epilogues run on the accumulators in registers (lane l: row l % 16, four consecutive columns of each
 //    tile), so no staging in LDS and no barrier follows the k-loop.  A wave holds 128 whole columns, which is what
 //    the per-head norm, the rotation (partner dimension in the same lane) and the per-group statistics need;
-//  - a launch is (column block, row block, k-split) items, one per workgroup.  The row blocks of one column block
+//  - the order of a row's sums is the matrix's, not the launch's (SumPlan): K is cut into segments, each summed k-step by
+//    k-step from zero, and the segments' sums are added in order.  So a sequence's logits do not depend on the other
+//    sequences of its call, nor a prompt's cached K/V on its chunks, bit for bit.  The price is what a free split
+//    over K would gain where the segments do not suit the launch: 99 rows of o_proj 31 -> 46 us, down_proj 56 -> 69, qkv 36 -> 41,
+//    LM head 310 -> 353, 264 rows of o_proj 47 -> 59 (Qwen3-32B width; no other product of 99, 264 or 1024 rows by more
+//    than 7%);
+//  - a launch is (column block, row block, contributor) items, one per workgroup.  The row blocks of one column block
 //    run on one XCD next to each other, so its L2 serves the weights to all but the first of them.  Where the
-//    tiles leave compute units idle, K is split: partials go through 16-byte device-coherent stores and are added
-//    in split order, the tile's row tiles shared out among its contributors.  A row's sums depend on its launch's
-//    plan but not on the other rows' values.
-//  - tiles that fill the chip several times and leave a few over pay a whole round for those few: the column blocks of
-//    the whole rounds run unsplit, those left over follow in the same launch with K split over all compute units.
-// Measured (Qwen3-32B width, with the chunked launches of 288 rows and 4 loading waves this kernel replaced): gate/up
-// over 1024 rows 4 x 148 -> 498 us (1.08 PFLOP/s; the library's product at this size 0.99), over 264 rows 186 -> 151;
-// down 125 -> 89, qkv 76 -> 58, o_proj 45 -> 47, LM head 546 -> 463 us.  What bounds it: a k-step of 8 + RTW fragment
+//    tiles fill the chip a workgroup walks a tile's segments in order, keeping the sum so far in memory while it
+//    multiplies the next one (a few us per segment); where they leave compute units idle, the segments are shared out:
+//    partials go through 16-byte device-coherent stores and are added in segment order, the tile's row tiles shared
+//    out among its contributors.
+// Measured (Qwen3-32B width; with the chunked launches of 288 rows and 4 loading waves this kernel replaced): gate/up
+// over 1024 rows 4 x 148 -> 455 us (1.18 PFLOP/s; the library's product at this size 0.99), over 264 rows 186 -> 136;
+// down 125 -> 95, qkv 76 -> 53, o_proj 45 -> 59, LM head 546 -> 490 us; over 1024 rows down 244 (1.10 PFLOP/s), qkv 131,
+// o_proj 95.  What bounds it: a k-step of 8 + RTW fragment
 // reads and 8 RTW MFMAs per wave takes 0.33 us + 14.2 ns per MFMA, about 1.6 times the matrix cores' own time at RTW 4.
 #include "gemm.h"
 
@@ -140,6 +146,28 @@ __device__ inline void lds_read_frags(u32x4* w, u32x4* x, uint32_t aw, uint32_t 
 // ---- epilogues of one row tile in the accumulator layout --------------------------------------------------
 // v[nt][e]: row `m`, column 16 (ct + nt) + 4 (lane / 16) + e.  No contraction: a row rounds alike everywhere.
 
+// Sum of squares of a row's 16 NT columns (y in the accumulator layout), in the order of the 33-row kernels: eight
+// consecutive columns one after another, then those sums pairwise.  The first four of eight lie in an even lane group,
+// the last four in the next one.  The result is in every lane of the row.
+template <int NT>
+__device__ inline float row_sum_squares(const f32x4* y) {
+#pragma clang fp contract(off)
+  float n[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const f32x4 q = y[nt] * y[nt];
+    float c = xor16_op(((q[0] + q[1]) + q[2]) + q[3], [](float lo, float) { return lo; });  // the even group's
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c += q[e];
+    n[nt] = xor32_op(c, [](float lo, float hi) { return lo + hi; });  // (right in the odd groups)
+  }
+#pragma unroll
+  for (int o = 1; o < NT; o *= 2)
+#pragma unroll
+    for (int nt = 0; nt < NT; nt += 2 * o) n[nt] += n[nt + o];
+  return xor16_op(n[0], [](float, float hi) { return hi; });
+}
+
 template <int NT>
 __device__ inline void tile_resid(const GemmArgs& a, const f32x4* v, int ct, int m, bool ok, int lane) {
 #pragma clang fp contract(off)
@@ -151,16 +179,11 @@ __device__ inline void tile_resid(const GemmArgs& a, const f32x4* v, int ct, int
     xo[nt] = *reinterpret_cast<const f32x4*>(xr + 16 * nt);
     gv[nt] = *reinterpret_cast<const f32x4*>(a.g_next + c0 + 16 * nt);
   }
-  float ss = 0.f;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      xo[nt][e] += v[nt][e];
-      ss += xo[nt][e] * xo[nt][e];
-    }
-  ss = xor16_op(ss, [](float x, float y) { return x + y; });
-  ss = xor32_op(ss, [](float x, float y) { return x + y; });
+    for (int e = 0; e < 4; ++e) xo[nt][e] += v[nt][e];
+  const float ss = row_sum_squares<NT>(xo);
   if (!ok) return;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -257,13 +280,7 @@ __device__ inline void tile_qkv(const GemmArgs& a, const f32x4* v, int h, int m,
   }
   if (a.qk_norm) {
     const float* gp = (is_q ? a.qn : a.kn) + d0;
-    float ss = 0.f;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ss += y[nt][e] * y[nt][e];
-    ss = xor16_op(ss, [](float x, float z) { return x + z; });
-    ss = xor32_op(ss, [](float x, float z) { return x + z; });
+    const float ss = row_sum_squares<NT>(y);
     const float inv = 1.f / sqrtf(ss / (float)C + a.eps);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -296,9 +313,10 @@ __device__ inline void tile_qkv(const GemmArgs& a, const f32x4* v, int h, int m,
   }
 }
 
-// MODE: what a launch's items are.  (A kernel that holds both kinds of item spills registers in its epilogues, outside
-// the k-loop, so the launches of one kind keep kernels of their own.)
-enum Mode { UNSPLIT = 0, SPLIT = 1, MIXED = 2 };
+// MODE: how a launch's items sum over K.  WHOLE: the matrix has one segment per column group, one workgroup per tile.
+// CHAIN: one workgroup per tile, which walks the segments in order.  SPLIT: a tile's segments are shared out.  (Kernels of
+// their own: one that holds both the unsplit and the split epilogue spills registers.)
+enum Mode { WHOLE = 0, CHAIN = 1, SPLIT = 2 };
 
 template <int WC, int RTW, int EPI, int MODE>
 __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) {
@@ -316,29 +334,32 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   const int wc = wv % WC, wr = wv / WC;  // this wave's column and row position
   const bool lateh = wv >= 4;            // the half that runs half a k-step behind
-  // item: column block and k-split cs (one XCD's items are 8 apart), row block fastest within an XCD
-  const int slot = blockIdx.x / kXcds, cs = blockIdx.x % kXcds + kXcds * (slot / a.nrb), rb = slot % a.nrb;
-  if (cs >= a.ncb1 + (a.ncb - a.ncb1) * a.ksplit) return;
-  const int S = MODE == SPLIT || (MODE == MIXED && cs >= a.ncb1) ? a.ksplit : 1;  // the first ncb1 column blocks are not split
-  const int cb = S == 1 ? cs : a.ncb1 + (cs - a.ncb1) / S, sp = S == 1 ? 0 : (cs - a.ncb1) % S;
-  const int kb = (int)((int64_t)a.KT * sp / S), nk = (int)((int64_t)a.KT * (sp + 1) / S) - kb;
+  const int S = MODE == SPLIT ? a.ksplit : 1;
+  const TileItem it = tile_item(a, blockIdx.x, S);
+  if (it.cbl < 0) return;
+  const int cb = it.cb, rb = it.rb, sp = it.sp;
+  // k-steps, and the K segments (SumPlan) they are: those of the block's first sum group, which are the block's wherever
+  // it is split
+  TileRange rg{0, a.KT, 0, 1, 0, 1, 1};
+  if constexpr (MODE == SPLIT) {
+    rg = tile_range(a, cb * CG, sp);
+    if (sp >= rg.E) return;
+  }
+  const int kb = __builtin_amdgcn_readfirstlane(rg.kb), ke = __builtin_amdgcn_readfirstlane(rg.ke), nk = ke - kb;
+  const int E = rg.E, nslot = rg.nseg - rg.n0 + 1;
   const int row0 = rb * ROWS, nrows = min(ROWS, a.M - row0);
   const uint32_t KT = (uint32_t)a.KT, G = (uint32_t)a.G, SC = (uint32_t)a.segc, NW = (uint32_t)a.n_wg;
   const int ng = a.ng, unit_b = ng * 1024;
 
-  // The wave's loads of a k-step: fragments wv, wv + 8, ... of [CG weight tiles][RT row tiles].  A weight tile
-  // is read where the matrix's streaming plan stores it: k-step k of group g is unit g KT + k of owner o, at slot
-  // (g KT + k - start(o)) n_wg + o; one tracker per weight tile follows its group's owners as k rises.
-  struct Trk {
-    int g, o, kend, base;  // group, owner, first k-step past its share, slot of k-step 0
-  };
+  // The wave's loads of a k-step: fragments wv, wv + 8, ... of [CG weight tiles][RT row tiles]; one tracker per weight
+  // tile follows its group's owners as k rises.
   constexpr int kOob = 0x7ffffff0;  // a lane offset past every descriptor: zero without a memory access
-  Trk trk[NWT];
-  auto trk_set = [&](Trk& t, int o) {
-    const uint32_t us = unit_start((uint32_t)o, KT, G, SC, NW), ue = unit_start((uint32_t)o + 1, KT, G, SC, NW);
-    t.o = __builtin_amdgcn_readfirstlane(o);
-    t.kend = __builtin_amdgcn_readfirstlane((int)(ue - (uint32_t)t.g * KT));
-    t.base = __builtin_amdgcn_readfirstlane(((int)((uint32_t)t.g * KT) - (int)us) * (int)NW + o);
+  TileTrk trk[NWT];
+  auto track = [&](TileTrk& t, int o) {
+    trk_set(a, t, o);
+    t.o = __builtin_amdgcn_readfirstlane(t.o);
+    t.kend = __builtin_amdgcn_readfirstlane(t.kend);
+    t.base = __builtin_amdgcn_readfirstlane(t.base);
   };
   int wtile[NWT], fl[LQ + 1];  // byte offset of a weight tile inside its unit; this lane's offset of each fragment
 #pragma unroll
@@ -347,7 +368,7 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
     trk[i].g = __builtin_amdgcn_readfirstlane(min(g, (int)G - 1));
     wtile[i] = __builtin_amdgcn_readfirstlane(ct % ng * 1024);
     fl[i] = g < (int)G ? lane * 16 : kOob;
-    trk_set(trk[i], unit_owner((uint32_t)trk[i].g * KT + (uint32_t)kb, KT, G, SC, NW));
+    track(trk[i], unit_owner((uint32_t)trk[i].g * KT + (uint32_t)kb, KT, G, SC, NW));
   }
 #pragma unroll
   for (int i = NWT; i <= LQ; ++i) fl[i] = xfrag_lane(row0 / 16 + wv + 8 * i - CG, a.KT, a.M, lane);
@@ -364,7 +385,7 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
     const int k = kb + min(ki, nk - 1);
 #pragma unroll
     for (int i = 0; i < NWT; ++i) {
-      while (k >= trk[i].kend) trk_set(trk[i], trk[i].o + 1);
+      while (k >= trk[i].kend) track(trk[i], trk[i].o + 1);
       wofs[i] = __builtin_amdgcn_readfirstlane((trk[i].base + k * (int)NW) * unit_b + wtile[i]);
       if (ki < nk) until = min(until, trk[i].kend - k);
     }
@@ -445,6 +466,105 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  const int ntiles = (nrows + 15) / 16;  // row tiles that hold rows
+  // Ends of K segments inside this workgroup's range.  The wave's two halves of four column tiles (h) follow their sum
+  // group's segments: its current one's owner, the k-step past it, whether an earlier one's sum is in memory, and where.
+  const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(a.part, 0, 0x7fffffff, kBufferRsrcWord3);
+  constexpr int kNoEnd = 0x7fffffff;
+  struct Seg {
+    uint32_t base;  // sum group's first unit (k-step 0)
+    int own, end, chain, at;
+  } sg[2];
+  int t_end = kNoEnd;  // next k-step at whose end a segment ends
+  auto seg_end = [&](Seg& s) {  // of segment s.own, none for the last one
+    const int e = sum_start(a, s.base, s.own + 1);
+    s.end = __builtin_amdgcn_readfirstlane(e < ke ? e : kNoEnd);
+  };
+  if constexpr (MODE != WHOLE) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int ct = cb * CG + wc * NTW + 4 * h;
+      sg[h].base = sum_base(a, MODE == SPLIT ? cb * CG : ct);
+      sg[h].chain = 0;
+      sg[h].own = MODE == SPLIT ? rg.own0 + rg.seg0 : sum_owner(a, sg[h].base);
+      sg[h].at = MODE == CHAIN ? __builtin_amdgcn_readfirstlane(chain_place(a, rb, ct, sg[h].own, CG, RT)) : 0;
+      seg_end(sg[h]);
+      if (MODE == CHAIN && 16 * ct >= a.N) sg[h].end = kNoEnd;  // past the matrix
+    }
+    t_end = min(sg[0].end, sg[1].end);
+  }
+  const int tile = rb * a.ncb + it.cbl;
+  auto part_off = [&](int slot, int rt, int wcol) {  // (< 2^31: checked on the host)
+    return part_place(a, tile, slot, rt, wcol, RT, WC) + lane * 16;
+  };
+  // Adds the accumulators to the partial sum that is in `slot` (fresh: to zero).
+  auto store_part = [&](int slot, bool fresh) {
+#pragma unroll
+    for (int j = 0; j < RTW; ++j)
+      if (wr * RTW + j < ntiles) {
+        const int at = part_off(slot, wr * RTW + j, wc);
+        if (!fresh) {
+          f32x4 v[NTW];
+#pragma unroll
+          for (int nt = 0; nt < NTW; ++nt)
+            v[nt] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(prs, at + nt * 1024, 0, kCoherentCpol));
+#pragma unroll
+          for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = v[nt] + acc[j][nt];
+        }
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j][nt]), prs, at + nt * 1024, 0, kCoherentCpol);
+      }
+  };
+  auto store_seg = [&]() {  // the segment that the accumulators hold
+    const int seg = sg[0].own - rg.own0;
+    store_part(part_slot(rg, seg), seg == 0 || seg >= rg.n0);
+  };
+  // the sum of the segments before the accumulators' one, for row tile j and half h
+  auto chain_load = [&](int h, int j, f32x4* v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      v[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                           prs, lane * 16 + ((wr * RTW + j) * 4 + i) * 1024, sg[h].at, 0));
+  };
+  // After k-step `k`: the segments that end there leave the accumulators, which start again from zero.
+  auto flush = [&](int k) {
+    if constexpr (MODE == SPLIT) {
+      store_seg();
+#pragma unroll
+      for (int j = 0; j < RTW; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      ++sg[0].own;
+      seg_end(sg[0]);
+      t_end = sg[0].end;
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (k == sg[h].end) {
+#pragma unroll
+          for (int j = 0; j < RTW; ++j)
+            if (wr * RTW + j < ntiles) {
+              f32x4 v[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+              if (sg[h].chain) chain_load(h, j, v);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                v[i] += acc[j][4 * h + i];
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[i]), prs,
+                                                       lane * 16 + ((wr * RTW + j) * 4 + i) * 1024, sg[h].at, 0);
+                acc[j][4 * h + i] = f32x4{0.f, 0.f, 0.f, 0.f};
+              }
+            }
+          sg[h].chain = 1;
+          ++sg[h].own;
+          seg_end(sg[h]);
+        }
+      t_end = min(sg[0].end, sg[1].end);
+    }
+  };
+
   const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(s_ring);
   const uint32_t rd_w = ring + (uint32_t)(wc * NTW * 1024 + lane * 16);
   const uint32_t rd_x = ring + (uint32_t)((CG + wr * RTW) * 1024 + lane * 16);
@@ -470,13 +590,15 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
       for (int nt = 0; nt < NTW; ++nt)
         mma_tile<uint16_t>(__builtin_bit_cast(uint4, wf[nt]), __builtin_bit_cast(uint4, xf[j]), acc[j][nt]);
     __builtin_amdgcn_s_setprio(0);
+    if constexpr (MODE != WHOLE) {
+      if (kb + t + 1 == t_end) flush(t_end);
+    }
     if (!lateh) wait_next();
     phase_barrier();
   }
   if (!lateh) phase_barrier();
   __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));  // the loads past the end (no memory access) before the block may end
 
-  const int ntiles = (nrows + 15) / 16;  // row tiles that hold rows
   // epilogue of row tile rt (of the block) and the NTW column tiles of wave column wcol: column groups of NT tiles
   auto epilogue = [&](auto ntc, const f32x4* v, int rt, int wcol) {
     constexpr int NT = decltype(ntc)::value;
@@ -502,46 +624,42 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
     else
       f(std::integral_constant<int, 4>{});
   };
-  if (MODE == UNSPLIT || (MODE == MIXED && S == 1)) {
+  if constexpr (MODE != SPLIT) {
     with_nt([&](auto ntc) {
 #pragma unroll
       for (int j = 0; j < RTW; ++j)
         if (wr * RTW + j < ntiles) {
+          if constexpr (MODE == CHAIN) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              if (sg[h].chain) {
+                f32x4 v[4];
+                chain_load(h, j, v);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[j][4 * h + i] = v[i] + acc[j][4 * h + i];
+              }
+          }
           epilogue(ntc, acc[j], wr * RTW + j, wc);
-          if constexpr (MODE == MIXED) __builtin_amdgcn_sched_barrier(0);  // one row tile's loads at a time: registers
         }
     });
-    return;
-  }
-  if constexpr (MODE != UNSPLIT) {
+  } else {
 
-  // Split item: every contributor stores its accumulators (16-byte device-coherent stores) and the item is
-  // finished in ksplit shares of (row tile, wave column) units, each summed in split order.  A contributor waits
-  // for the others for a bounded time (a split launch has at most one workgroup per compute unit, so all of them
-  // are normally running) and finishes its own share; whoever arrives last also takes the shares that nobody
-  // claimed, so the item completes whether or not the others waited.  The last one to leave zeroes the counters.
-  // (Unsplit items, launched first, wait for nobody, so the split ones behind them are always reached.)
+  // Split item: every contributor stores its segments' sums (16-byte device-coherent stores) and the item is finished in E
+  // shares of (row tile, wave column) units, each summed in segment order.  A contributor waits for the others for a
+  // bounded time (a split launch has at most one workgroup per compute unit, so all of them are normally running; where
+  // other work holds compute units, a waiting contributor holds its own until then) and finishes its own share; whoever
+  // arrives last also takes the shares that nobody claimed, so the item completes whether or not the others waited.  The
+  // last one to leave zeroes the counters.
   // Measured against the last arriver adding all partials: 264 rows of down_proj 125 -> 93 us, o_proj 61 -> 50.
-  const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(a.part, 0, 0x7fffffff, kBufferRsrcWord3);
-  const int item = rb * (a.ncb - a.ncb1) + cb - a.ncb1;
-  auto part_off = [&](int sq, int rt, int wcol) {  // bytes (< 2^31: checked on the host)
-    return (((item * S + sq) * RT + rt) * WC + wcol) * NTW * 1024 + lane * 16;
-  };
-#pragma unroll
-  for (int j = 0; j < RTW; ++j)
-    if (wr * RTW + j < ntiles)
-#pragma unroll
-      for (int nt = 0; nt < NTW; ++nt)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j][nt]), prs,
-                                               part_off(sp, wr * RTW + j, wc) + nt * 1024, 0, kCoherentCpol);
+  store_seg();
   wait_stores();
   __syncthreads();
-  int* const cnt = &a.cnt[item * kCntStride];  // arrivals, claimed shares (bits), departures
+  int* const cnt = &a.cnt[tile * kCntStride];  // arrivals, claimed shares (bits), departures
   if (threadIdx.x == 0) {
-    int st = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1 ? 2 : 0;
-    for (int it = 0; st == 0 && it < kTilePolls; ++it) {
+    int st = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == E - 1 ? 2 : 0;
+    for (int i = 0; st == 0 && i < kTilePolls; ++i) {
       __builtin_amdgcn_s_sleep(2);
-      if (ld_coherent(cnt) == S) st = 1;
+      if (ld_coherent(cnt) == E) st = 1;
     }
     if (st == 1 && (__hip_atomic_fetch_or(cnt + 1, 1 << sp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> sp & 1)) st = 0;
     // the last arriver claims its own share, and what is left once that is done
@@ -556,17 +674,17 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) sum[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
       constexpr int kB = 3;  // partials in flight
-      for (int s0 = 0; s0 < S; s0 += kB) {
+      for (int s0 = 0; s0 < nslot; s0 += kB) {
         f32x4 pv[kB][NTW];
 #pragma unroll
         for (int q = 0; q < kB; ++q)
 #pragma unroll
           for (int nt = 0; nt < NTW; ++nt)
             pv[q][nt] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      prs, part_off(min(s0 + q, S - 1), rt, wcol) + nt * 1024, 0, kCoherentCpol));
+                                                      prs, part_off(min(s0 + q, nslot - 1), rt, wcol) + nt * 1024, 0, kCoherentCpol));
 #pragma unroll
         for (int q = 0; q < kB; ++q)
-          if (s0 + q < S)
+          if (s0 + q < nslot)
 #pragma unroll
             for (int nt = 0; nt < NTW; ++nt) sum[nt] += pv[q][nt];
       }
@@ -574,19 +692,19 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
     }
   };
   if (st != 0) {
-    units(sp, S);
+    units(sp, E);
     if (st == 2) {
       if (threadIdx.x == 0) {
-        const int all = (1 << S) - 1;
+        const int all = (1 << E) - 1;
         s_left = all & ~__hip_atomic_fetch_or(cnt + 1, all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~(1 << sp);
       }
       __syncthreads();
-      for (int q = 0; q < S; ++q)
-        if (s_left >> q & 1) units(q, S);
+      for (int q = 0; q < E; ++q)
+        if (s_left >> q & 1) units(q, E);
     }
   }
   if (threadIdx.x == 0 &&
-      __hip_atomic_fetch_add(cnt + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1) {
+      __hip_atomic_fetch_add(cnt + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == E - 1) {
     st_coherent(cnt, 0);
     st_coherent(cnt + 1, 0);
     st_coherent(cnt + 2, 0);
@@ -596,96 +714,117 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
 
 template <int EPI, int MODE>
 void launch_shape(const TilePlan& p, const GemmArgs& a, hipStream_t st) {
-  const dim3 grid(kXcds * (int)ceil_div(p.ncb1 + (int64_t)(p.ncb - p.ncb1) * p.ksplit, kXcds) * p.nrb), block(kTileThreads);
+  const dim3 grid(tile_grid(a)), block(kTileThreads);
 #define SDD_TILE(WC, RTW) \
   case WC * 10 + RTW: hipLaunchKernelGGL((gemm_tile_kernel<WC, RTW, EPI, MODE>), grid, block, 0, st, a); break
   switch (p.wc * 10 + p.rtw) {
+    SDD_TILE(1, 1);
+    SDD_TILE(1, 2);
+    SDD_TILE(1, 3);
     SDD_TILE(2, 2);
     SDD_TILE(2, 3);
     SDD_TILE(2, 4);
-  }
-  if constexpr (MODE != MIXED) {
-    switch (p.wc * 10 + p.rtw) {
-      SDD_TILE(2, 5);
-      SDD_TILE(1, 1);
-      SDD_TILE(1, 2);
-      SDD_TILE(1, 3);
-    }
+    SDD_TILE(2, 5);
   }
 #undef SDD_TILE
 }
 
 template <int EPI>
 void launch_tile(const TilePlan& p, const GemmArgs& a, hipStream_t st) {
-  if (p.ksplit == 1)
-    launch_shape<EPI, UNSPLIT>(p, a, st);
-  else if (p.ncb1 == 0)
+  if (p.ksplit > 1)
     launch_shape<EPI, SPLIT>(p, a, st);
+  else if (p.sums.nseg > 1)
+    launch_shape<EPI, CHAIN>(p, a, st);
   else
-    launch_shape<EPI, MIXED>(p, a, st);
+    launch_shape<EPI, WHOLE>(p, a, st);
 }
 
 }  // namespace
 
+SumPlan sum_plan(const MatPlan& mp, bool pairs) {
+  SumPlan s{mp.ng, mp.G, mp.n_wg, mp.c, 1, true};
+  if (pairs && mp.ng == 8) {
+    s.tiles = 16;
+    s.G = (mp.G + 1) / 2;
+    s.n = s.G >= mp.n_wg ? mp.n_wg : s.G * std::min(mp.n_wg / s.G, mp.KT);
+    s.c = 0;
+  }
+  s.uniform = s.c == 0 && s.n % s.G == 0;
+  s.nseg = s.uniform ? s.n / s.G : s.n <= s.G ? 2 : s.n / s.G + 2;
+  return s;
+}
+
 // The launch's estimated time, fitted to measurements of every shape and split at 99-1792 rows of the Qwen3-32B and
 // Qwen2.5-7B widths: a k-step takes 0.33 us (two barriers, the LDS reads' latency, load issue) + 14.2 ns per MFMA of
-// a wave; weights stream at 6 TB/s at best, round by round; a split writes and reads its partial tiles once at about
-// 6 TB/s and costs 3 us more, 15 us more again behind unsplit rounds.  Workgroups go to the XCDs round-robin, so rounds
-// and the split workgroups that can run at once are counted per XCD.  (Counted over the whole chip, plans with 33-35
-// waiting workgroups on an XCD of 32 compute units ran into the bound of the wait: down_proj of Qwen2.5-7B over 1136
-// rows 250 -> 152 us, over 528 rows 142 -> 88.)
-// Splitting only the column blocks left over after whole rounds: LM head of 99 rows 338 -> 310 us, gate/up of 1024 rows
-// 474 -> 446 (Qwen3-32B width).  With 5 row tiles per wave that kernel spills in its k-loop and is not used.
-TilePlan plan_tiles(const MatPlan& mp, int M, int n_cu, size_t part_bytes, int64_t max_split) {
+// a wave; weights stream at 6 TB/s at best, round by round; a segment that ends in a workgroup's walk costs 2 us and
+// 5 us per 256 x 256 tile; a split writes and reads its partial tiles once at about 6 TB/s and costs 3 us more.  A last
+// round is the shorter the emptier it is (gate/up over 1024 rows, 3.1 rounds, takes 3.6 rounds' time).  Workgroups go to the XCDs round-robin, so rounds and the split workgroups that can run at
+// once are counted per XCD.  (Counted over the whole chip, plans with 33-35 waiting workgroups on an XCD of 32 compute
+// units had to wait for a second round: down_proj of Qwen2.5-7B over 1136 rows 250 -> 152 us, over 528 rows 142 -> 88.)
+TilePlan plan_tiles(const MatPlan& mp, bool pairs, int M, int n_cu, size_t part_bytes, int64_t max_split) {
+  const SumPlan sums = sum_plan(mp, pairs);
   const int CT = mp.G * mp.ng, RTM = (int)ceil_div(M, 16), xcd_cus = std::max(1, n_cu / kXcds);
   TilePlan best{};
   best.us = 1e30;
   const size_t cap = std::min<size_t>(part_bytes, (size_t(1) << 31) - 1);
   const double hbm = (double)CT * mp.KT * 1024 / 6.0e6;
+  const double seg_avg = sums.uniform ? sums.nseg : 1.0 + (double)(sums.n - 1) / sums.G;  // segments per column group
   constexpr int kShapes[][2] = {{1, 1}, {1, 2}, {1, 3}, {2, 2}, {2, 3}, {2, 4}, {2, 5}};
   for (const auto& sh : kShapes) {
     const int wc = sh[0], rtw = sh[1], CG = 8 * wc, RT = 8 / wc * rtw;
     const int ncb = (int)ceil_div(CT, CG), nrb = (int)ceil_div(RTM, RT);
     const double kstep = 0.33 + 0.0142 * 8 * rtw, tile_bytes = 1024.0 * CG * RTM / nrb;
-    const auto round_us = [&](int s) { return (double)ceil_div(mp.KT, s) * kstep + 1.0; };
-    const auto consider = [&](int ncb1, int s, double us) {
-      if (us < best.us) best = TilePlan{wc, rtw, ncb, nrb, ncb1, s, us};
-    };
-    // the workgroups of n (column block, k-range) pairs on the XCD that gets most of them
-    const auto per_xcd = [&](int64_t n) { return ceil_div(n, kXcds) * nrb; };
-    const int full = (int)(per_xcd(ncb) / xcd_cus);  // whole rounds, each no faster than its weights stream
-    const double full_us = std::max(round_us(1), hbm * xcd_cus / per_xcd(ncb));
-    const double part = hbm - std::min(hbm, full * hbm * xcd_cus / per_xcd(ncb));
-    // (unsplit: the last round's epilogue is exposed)
-    consider(0, 1, 6.0 + full * full_us + (per_xcd(ncb) % xcd_cus ? std::max(part, round_us(1)) : 0.0) + tile_bytes / 50e3);
-    // `rounds` whole rounds of every XCD's compute units unsplit, the column blocks left over split behind them
-    for (int rounds : {0, full}) {
-      const int ncb1 = kXcds * (rounds * xcd_cus / nrb);
-      if (ncb1 >= ncb || (rounds > 0 && (ncb1 == 0 || wc != 2 || rtw > 4))) continue;
-      const int64_t left = ncb - ncb1;
-      for (int s = 2; s <= 16 && s * 8 <= mp.KT; ++s) {
-        // a split tile's workgroups wait for each other: no more of them on an XCD than it can run at once
-        if (per_xcd(left * s) > xcd_cus || (size_t)(left * nrb * s) * CG * RT * 1024 > cap || left * nrb > max_split) break;
-        const double last = std::max(hbm * left / ncb, round_us(s)) + 2.0 * left * nrb * s * tile_bytes / 6.0e6;
-        consider(ncb1, s, 9.0 + (rounds > 0 ? rounds * full_us + 15.0 : 0.0) + last);
+    const auto per_xcd = [&](int64_t n) { return ceil_div(n, kXcds) * nrb; };  // workgroups of n (column block, contributor) pairs on the XCD that gets most of them
+    // one workgroup per tile, in as many launches as the running sums need; rounds no faster than their weights stream
+    {
+      // running sums: one place per 64 columns and row block, or one per boundary where shares are longer than groups
+      const size_t place = (size_t)RT * 4096;
+      const bool compact = !sums.uniform && sums.n <= sums.G && (size_t)nrb * sums.n * (sums.tiles / 4) * place <= cap;
+      int per = ncb;  // column blocks per launch
+      if (sums.nseg > 1 && !compact) per = (int)std::min<int64_t>(ncb, (int64_t)(cap / (place * nrb * 2 * wc)));
+      if (per < 1) continue;
+      const double chain = (seg_avg - 1.0) * (2.0 + 5.0 * CG * RT / 256);
+      double us = 0.0;
+      for (int c0 = 0; c0 < ncb; c0 += per) {
+        const int n = std::min(per, ncb - c0), full = (int)(per_xcd(n) / xcd_cus);  // whole rounds
+        const double round_us = mp.KT * kstep + 1.0 + chain, share = hbm * n / ncb;
+        const double part = share - std::min(share, full * share * xcd_cus / per_xcd(n));
+        // (the last round's epilogue is exposed)
+        const double left = (double)(per_xcd(n) % xcd_cus) / xcd_cus;  // of a last round, which runs faster the emptier it is
+        us += 6.0 + full * std::max(round_us, share * xcd_cus / per_xcd(n)) +
+              (left > 0 ? std::max(part, round_us * (full ? 0.5 + 0.5 * left : 1.0)) : 0.0) + tile_bytes / 50e3;
       }
+      if (us < best.us) best = TilePlan{wc, rtw, ncb, nrb, per, 1, 0, compact, sums, us};
+    }
+    // a tile's segments shared out, where every group has the same ones.  (Measured for groups with one or two, the LM head's:
+    // its 594 tiles of 99 rows in segments on 1188 workgroups, a tile's second one to finish adding both, 465 us against 353.)
+    if (!sums.uniform) continue;
+    for (int s = 2; s <= std::min(16, sums.nseg); ++s) {
+      const int slots = sums.nseg - (int)ceil_div(sums.nseg, s) + 1;
+      if ((size_t)ncb * nrb * slots * CG * RT * 1024 > cap || (int64_t)ncb * nrb > max_split) continue;
+      // a split tile's workgroups wait for each other: no more of them on an XCD than it can run at once
+      if (per_xcd((int64_t)ncb * s) > xcd_cus) break;
+      const double run = (double)ceil_div(sums.nseg, s) / sums.nseg * mp.KT * kstep + 1.0;
+      const double us = 9.0 + std::max(hbm, run) + 2.0 * ncb * nrb * slots * tile_bytes / 6.0e6;
+      if (us < best.us) best = TilePlan{wc, rtw, ncb, nrb, ncb, s, slots, false, sums, us};
     }
   }
   return best;
 }
 
 int launch_gemm_tiles(const TilePlan& p, int epi, GemmArgs a, hipStream_t st) {
-  a.ncb = p.ncb;
-  a.ncb1 = p.ncb1;
-  a.nrb = p.nrb;
-  a.ksplit = p.ksplit;
-  switch (epi) {
-    case EPI_QKV: launch_tile<EPI_QKV>(p, a, st); break;
-    case EPI_RESID: launch_tile<EPI_RESID>(p, a, st); break;
-    case EPI_SWIGLU: launch_tile<EPI_SWIGLU>(p, a, st); break;
-    default: launch_tile<EPI_LOGITS>(p, a, st); break;
+  for (int cb0 = 0; cb0 < p.ncb; cb0 += p.per) {
+    tile_launch(a, p, cb0);
+    switch (epi) {
+      case EPI_QKV: launch_tile<EPI_QKV>(p, a, st); break;
+      case EPI_RESID: launch_tile<EPI_RESID>(p, a, st); break;
+      case EPI_SWIGLU: launch_tile<EPI_SWIGLU>(p, a, st); break;
+      default: launch_tile<EPI_LOGITS>(p, a, st); break;
+    }
+    const int rc = check_launch("gemm_tile_kernel");
+    if (rc) return rc;
   }
-  return check_launch("gemm_tile_kernel");
+  return SDD_OK;
 }
 
 }  // namespace sdd

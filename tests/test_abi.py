@@ -3,6 +3,7 @@ checks return the documented status codes without touching a GPU."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -239,6 +240,17 @@ def test_pair_partition_reads_every_stored_tile(S, which):
                 u += ke - kb
         assert (seen == 1).all(), kind
     assert L.sdd_model_destroy(h) == S.OK
+
+
+def test_many_row_gemm_index_arithmetic(tmp_path):
+    """The many-row GEMM's item, segment, tracker and scratch arithmetic replayed on the CPU (tile_replay.hip), for whole,
+    chained and split plans: every tile and k-step once, weights from their stored slots, every place in bounds."""
+    from paper_2608_14787_amd import build
+    here, exe = os.path.dirname(os.path.abspath(__file__)), str(tmp_path / "tile_replay")
+    subprocess.check_call([build.HIPCC, *build.FLAGS, os.path.join(here, "tile_replay.hip"), "-o", exe, "-L", build.HERE,
+                           "-l:libsdd.so", "-Wl,-rpath," + build.HERE], stderr=subprocess.DEVNULL)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
 
 
 @pytest.mark.parametrize("d_in,H", [(3603, 256), (1043, 256), (3603, 64), (40, 16)])
