@@ -363,7 +363,9 @@ typedef struct {
   float b4;
 } sdd_mlp;
 
-/* Workspace bytes for sdd_survival_mlp over n positions. */
+/* Workspace bytes for sdd_survival_mlp over n positions.  The workspace serves
+ * calls of any number of positions up to n, in any order, and those of other
+ * predictors whose workspace for as many positions is no larger. */
 int sdd_survival_workspace_bytes(const sdd_mlp* m, int n, size_t* bytes);
 
 /* Survival scores of n draft positions (Sec. 4.2: the marginal a_j or the

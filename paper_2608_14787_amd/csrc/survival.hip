@@ -36,6 +36,10 @@ constexpr int kRowTile = 64;   // positions per workgroup (4 waves x 16)
 constexpr int kKc = 128;       // k-chunk staged in LDS by layer 1
 constexpr int kMaxH = 256;
 constexpr int kCntLine = 32;  // ints per 128-byte line
+constexpr int kMaxCT = kMaxH / 16;
+// Row tiles per launch (4096 positions; more take several launches): bounds the counters, so that they lie at one place in
+// every workspace, whatever a call's positions and predictor.
+constexpr int kMaxRT = 64;
 
 struct MlpArgs {
   const uint16_t* hidden;  // [n][d_hid] bf16
@@ -50,10 +54,10 @@ struct MlpArgs {
   float* zpart;     // [rt][ct][64]
   // counters one 128-byte line apart (index x at [x * kCntLine]): the workgroups that count on them, and
   // those polling them, do so at about the same time, and device-scope atomics on one line serialize
-  int* cnt1;        // [rt][ct]
-  int* cnt3;        // [rt]
-  int* done1;       // [rt]: h1 tiles written
-  int* done2;       // [rt]: h2 tiles written
+  int* cnt1;        // [kMaxRT][kMaxCT]
+  int* cnt3;        // [kMaxRT]
+  int* done1;       // [kMaxRT]: h1 tiles written
+  int* done2;       // [kMaxRT]: h2 tiles written
   int* err;         // sticky: a wait ran past its bound
   float* log_score;
   float* logit;
@@ -144,7 +148,7 @@ __device__ void layer1_body(const MlpArgs& a, int bid, float* smem, int* s_flag)
   const int row_l = wave * 16 + lane % 16, col4 = 4 * (lane / 16);
   const int off = (((tile * a.S + s) * kRowTile + row_l) * 16 + col4) * 4;  // bytes (< 2^31: checked on the host)
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc), prs, off, 0, kCoherentCpol);
-  if (!arrive_last(&a.cnt1[tile * kCntLine], a.S, s_flag)) return;
+  if (!arrive_last(&a.cnt1[(rt * kMaxCT + ct) * kCntLine], a.S, s_flag)) return;
   // last split of this tile: sum the splits in order, bias, GELU
   // (16 splits' loads in flight at a time, added in split order)
   constexpr int kB = 16;
@@ -273,12 +277,14 @@ __global__ void __launch_bounds__(kMlpThreads) survival_kernel(MlpArgs a) {
   }
 }
 
+// The counters and the sticky error word come first, at offsets that no call changes: a call finds them as the one before
+// left them, however many positions that one had.
 struct MlpWs {
-  size_t part, h1, h2, zpart, cnt1, cnt3, done, total;
+  size_t cnt1, cnt3, done1, done2, err, part, h1, h2, zpart, total;
 };
 
-MlpWs mlp_ws(int n, int H, int S) {
-  const int RT = (int)ceil_div(n > 0 ? n : 1, kRowTile), CT = H / 16;
+MlpWs mlp_ws(int RT, int H, int S) {
+  const int CT = H / 16;
   MlpWs w{};
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -286,9 +292,12 @@ MlpWs mlp_ws(int n, int H, int S) {
     o += (bytes + 255) / 256 * 256;
     return at;
   };
-  w.cnt1 = take((size_t)RT * CT * kCntLine * sizeof(int));
-  w.cnt3 = take((size_t)RT * kCntLine * sizeof(int));
-  w.done = take((size_t)(2 * RT + 1) * kCntLine * sizeof(int));  // done1 [RT], done2 [RT], the sticky error word
+  constexpr size_t kLine = kCntLine * sizeof(int);
+  w.cnt1 = take(kMaxRT * kMaxCT * kLine);
+  w.cnt3 = take(kMaxRT * kLine);
+  w.done1 = take(kMaxRT * kLine);
+  w.done2 = take(kMaxRT * kLine);
+  w.err = take(kLine);
   w.part = take((size_t)RT * CT * S * kRowTile * 16 * sizeof(float));
   w.h1 = take((size_t)RT * kRowTile * H * sizeof(float));
   w.h2 = take((size_t)RT * kRowTile * H * sizeof(float));
@@ -299,9 +308,9 @@ MlpWs mlp_ws(int n, int H, int S) {
 
 // k-splits of layer 1: up to 512 workgroups in all (three fit a compute unit), each split a whole number of LDS
 // chunks; for few positions one chunk each, a chunk being a serial load, stage and multiply
-void layer1_splits(int n, int H, int d_in, int& S, int& kc_split) {
-  const int RT = (int)ceil_div(n > 0 ? n : 1, kRowTile), CT = H / 16;
-  int want = std::max(1, 512 / (RT * CT));
+void layer1_splits(int64_t RT, int H, int d_in, int& S, int& kc_split) {
+  const int64_t CT = H / 16;
+  const int want = (int)std::max<int64_t>(1, 512 / (RT * CT));
   kc_split = (int)ceil_div(ceil_div(d_in, want), kKc) * kKc;
   S = (int)ceil_div(d_in, kc_split);
 }
@@ -325,10 +334,10 @@ extern "C" int sdd_survival_workspace_bytes(const sdd_mlp* m, int n, size_t* byt
   SDD_REQUIRE(bytes != nullptr && n >= 0, "bad arguments");
   // fewer positions take more k-splits and can need more: a workspace for n serves every smaller call
   *bytes = 0;
-  for (int64_t k = n; k > -kRowTile; k -= kRowTile) {
+  for (int RT = 1; RT <= std::max<int64_t>(1, std::min<int64_t>(kMaxRT, ceil_div(n, kRowTile))); ++RT) {
     int S, kc;
-    layer1_splits((int)std::max<int64_t>(k, 1), m->H, m->d_hid + m->n_sc, S, kc);
-    *bytes = std::max(*bytes, mlp_ws((int)std::max<int64_t>(k, 1), m->H, S).total);
+    layer1_splits(RT, m->H, m->d_hid + m->n_sc, S, kc);
+    *bytes = std::max(*bytes, mlp_ws(RT, m->H, S).total);
   }
   return SDD_OK;
 }
@@ -341,8 +350,6 @@ extern "C" int sdd_survival_mlp(const sdd_mlp* m, const uint16_t* hidden, const 
   if (n == 0) return SDD_OK;
   SDD_REQUIRE(log_score && (m->d_hid == 0 || hidden) && (m->n_sc == 0 || scalars), "NULL input or output");
   MlpArgs a{};
-  a.hidden = hidden;
-  a.scalars = scalars;
   a.mu = m->mu;
   a.sigma = m->sigma;
   a.W1 = m->W1;
@@ -353,18 +360,19 @@ extern "C" int sdd_survival_mlp(const sdd_mlp* m, const uint16_t* hidden, const 
   a.b3 = m->b3;
   a.w4 = m->w4;
   a.b4 = m->b4;
-  a.n = n;
   a.d_hid = m->d_hid;
   a.n_sc = m->n_sc;
   a.d_in = m->d_hid + m->n_sc;
   a.H = m->H;
-  layer1_splits(n, a.H, a.d_in, a.S, a.kc_split);
-  const MlpWs L = mlp_ws(n, a.H, a.S);
+  const int RT = (int)ceil_div(n, kRowTile), CT = a.H / 16;
+  layer1_splits(RT, a.H, a.d_in, a.S, a.kc_split);
+  const MlpWs L = mlp_ws(std::min(RT, kMaxRT), a.H, a.S);
   SDD_REQUIRE(ws != nullptr && ws_bytes >= L.total, "predictor workspace needs %zu bytes, got %zu", L.total, ws_bytes);
   SDD_REQUIRE((uintptr_t)ws % 256 == 0, "workspace must be 256-byte aligned");
-  const int RT = (int)ceil_div(n, kRowTile), CT = a.H / 16;
   if ((int64_t)RT * CT * a.S * kRowTile * 16 * 4 >= (int64_t(1) << 31))
     return fail(SDD_EUNSUPPORTED, "%d positions exceed the 32-bit partial offsets", n);
+  if ((int64_t)RT * kRowTile * a.H * 4 >= (int64_t(1) << 31))
+    return fail(SDD_EUNSUPPORTED, "%d positions exceed the 32-bit activation offsets", n);
   char* w = reinterpret_cast<char*>(ws);
   a.part = reinterpret_cast<float*>(w + L.part);
   a.h1 = reinterpret_cast<float*>(w + L.h1);
@@ -372,16 +380,20 @@ extern "C" int sdd_survival_mlp(const sdd_mlp* m, const uint16_t* hidden, const 
   a.zpart = reinterpret_cast<float*>(w + L.zpart);
   a.cnt1 = reinterpret_cast<int*>(w + L.cnt1);
   a.cnt3 = reinterpret_cast<int*>(w + L.cnt3);
-  a.done1 = reinterpret_cast<int*>(w + L.done);
-  a.done2 = a.done1 + (size_t)RT * kCntLine;
-  a.err = a.done2 + (size_t)RT * kCntLine;
-  a.log_score = log_score;
-  a.logit = logit;
+  a.done1 = reinterpret_cast<int*>(w + L.done1);
+  a.done2 = reinterpret_cast<int*>(w + L.done2);
+  a.err = reinterpret_cast<int*>(w + L.err);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if ((int64_t)RT * kRowTile * a.H * 4 >= (int64_t(1) << 31))
-    return fail(SDD_EUNSUPPORTED, "%d positions exceed the 32-bit activation offsets", n);
-  prof_begin(PROF_MLP, st);
-  hipLaunchKernelGGL(survival_kernel, dim3(RT * CT * (a.S + 2)), dim3(kMlpThreads), 0, st, a);
-  prof_end(PROF_MLP, st);
-  return check_launch("survival_kernel");
+  for (int r0 = 0; r0 < n; r0 += kMaxRT * kRowTile) {
+    a.n = std::min(n - r0, kMaxRT * kRowTile);
+    a.hidden = hidden ? hidden + (size_t)r0 * m->d_hid : nullptr;
+    a.scalars = scalars ? scalars + (size_t)r0 * m->n_sc : nullptr;
+    a.log_score = log_score + r0;
+    a.logit = logit ? logit + r0 : nullptr;
+    prof_begin(PROF_MLP, st);
+    hipLaunchKernelGGL(survival_kernel, dim3((int)ceil_div(a.n, kRowTile) * CT * (a.S + 2)), dim3(kMlpThreads), 0, st, a);
+    prof_end(PROF_MLP, st);
+    if ((rc = check_launch("survival_kernel"))) return rc;
+  }
+  return SDD_OK;
 }

@@ -66,6 +66,31 @@ def test_survival_repeatable(sdd):
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
+def test_survival_workspace_shared_by_calls_of_any_size(sdd):
+    """One workspace, calls of more and of fewer positions in turn (around the 64-row tiles' edges) and of a narrower
+    predictor: each gives what a fresh workspace gives, bit for bit."""
+    x, y = W.survival_inputs(seed=6, n=528), W.survival_inputs(seed=7, n=100, d_hid=300, n_sc=0, H=48)
+    big, small = _mlp(sdd, x), _mlp(sdd, y)
+    ws = big.workspace(528)
+    dev = lambda b: torch.from_numpy(b.view(np.int16)).cuda().view(torch.bfloat16)  # noqa: E731
+    hx, sx, hy = dev(x.hidden_bits), torch.from_numpy(np.ascontiguousarray(x.scalars)).cuda(), dev(y.hidden_bits)
+    for n, other in ((528, 0), (32, 0), (528, 0), (65, 0), (64, 100), (1, 0), (129, 3), (528, 0)):
+        got = big(hx[:n], sx[:n].contiguous(), ws=ws)
+        want = big(hx[:n], sx[:n].contiguous(), ws=big.workspace(n))
+        assert torch.isfinite(got).all() and torch.equal(got, want), n
+        if other:
+            assert torch.equal(small(hy[:other], None, ws=ws), small(hy[:other], None, ws=small.workspace(other))), other
+
+
+def test_survival_many_positions(sdd):
+    """More positions than one launch takes (4096), the last launch a partial tile."""
+    x = W.survival_inputs(seed=8, n=4096 + 70, d_hid=40, n_sc=5, H=16)
+    x.w4 *= 20.0
+    ls, lg = _run(sdd, x)
+    rls, rlg = _ref(x)
+    assert np.abs(lg - rlg).max() <= TOL and np.abs(ls - rls).max() <= TOL
+
+
 @pytest.mark.parametrize("signal", [oracle.SIG_MARGINAL, oracle.SIG_CONDITIONAL])
 def test_survival_feeds_scheduler(sdd, signal):
     """Predictor scores of 8 blocks of 32 positions drive the two-gate scheduler (Sec. 4.2 settings:
