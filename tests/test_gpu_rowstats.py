@@ -156,6 +156,38 @@ def test_non_finite_in_a_stream_of_finite_vectors(sdd, dtype, V):
     np.testing.assert_allclose(lc.cpu().numpy()[:, [0, 2]], ref["log_conf"][:, [0, 2]], atol=2e-5, rtol=0)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [1000, 20488])
+def test_masked_vocabulary(sdd, dtype, V):
+    """Half of every third row at -inf and some of it NaN, whole rows of -inf and of NaN: the oracle's integers in every
+    mode, and finite rows between them untouched by it."""
+    g = np.random.default_rng(V + 1)
+    B, R = 8, 5
+    z = g.standard_normal((B, R, V)).astype(np.float32) * 3
+    z[:, ::3][g.random((B, 2, V)) < 0.5] = -np.inf
+    z[::2, 3][g.random((B // 2, V)) < 0.1] = np.nan
+    z[1, 1], z[5, 2] = -np.inf, np.nan
+    d = np.where(g.random((B, R - 1)) < 0.7, np.nan_to_num(z[:, :-1], nan=-1e9).argmax(-1), g.integers(0, V, (B, R - 1))).astype(np.int32)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    zt = torch.from_numpy(z).cuda().to(dt)
+    qt = torch.from_numpy(np.where(g.random((B, R - 1, V)) < 0.02, -np.inf, z[:, :-1])).cuda().to(dt)
+    zv, qv = zt.float().cpu().numpy(), qt.float().cpu().numpy()
+    u = g.random((B, R - 1)).astype(np.float32)
+    dd, uu = torch.from_numpy(d).cuda(), torch.from_numpy(u).cuda()
+    for mode, k, len_ in ((0, 1, 1.0), (1, 1, 1.0), (2, 4, 1.0), (3, 1, 0.3)):
+        kw = dict(q=qt, uniforms=uu) if mode == 1 else {}
+        ow = dict(q=qv, u=u) if mode == 1 else {}
+        L, nxt, fl = sdd.accept(dd, zt, mode, k=k, lenience=len_, **kw)
+        ref = oracle.accept(mode, d, zv, k=k, lenience=len_, **ow)
+        assert L.cpu().tolist() == ref["accepted_len"].tolist(), mode
+        assert nxt.cpu().tolist() == ref["next_token"].tolist(), mode
+        assert fl.cpu().tolist() == ref["flags"].tolist(), mode
+    sk, lc, _ = sdd.confidence_prefix(zt, R, 0.2 / V, log_conf=True)
+    ref = oracle.confidence_prefix(zv, R, 0.2 / V)
+    assert sk.cpu().tolist() == ref["skip_len"].tolist()
+    np.testing.assert_allclose(lc.cpu().numpy(), ref["log_conf"], atol=2e-5, rtol=0, equal_nan=True)
+
+
 @pytest.mark.parametrize("variant", ["literal", "boosted"])
 def test_confidence_full_size(sdd, variant):
     B, gamma, V = 16, 32, 151936
