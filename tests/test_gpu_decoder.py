@@ -72,8 +72,9 @@ def test_weight_generator_bit_identical(S):
     assert np.array_equal(lm, want)
 
 
-def _run_case(S, shape, prompt_len, gamma, seed, n_rounds=1, max_len=None, ws_rows=64):
-    """Prefill + verify rounds on the GPU and the oracle's cached route; returns per-round results."""
+def _run_case(S, shape, prompt_len, gamma, seed, n_rounds=1, max_len=None, ws_rows=64, chunks=None):
+    """Prefill (in a number of chunks that `chunks` holds, where given: one embedding launch each) + verify rounds on the GPU and the oracle's
+    cached route; returns per-round results."""
     print(f"case {shape} prompt={prompt_len} gamma={gamma} seed={seed} ws_rows={ws_rows}", flush=True)
     m = _gpu_model(S, shape)
     max_len = max_len or prompt_len + n_rounds * (gamma + 1) + 8
@@ -82,7 +83,11 @@ def _run_case(S, shape, prompt_len, gamma, seed, n_rounds=1, max_len=None, ws_ro
     om = oracle.Model(shape)
     okv = oracle.KV(om, max_len)
     toks = W.prompt(seed, prompt_len, shape.vocab)
+    S.profile_start(1, 64)
     kv.prefill(0, to_dev_i32(toks), ws)
+    n_chunks = S.profile_read(1)[0]
+    S.profile_stop()
+    assert chunks is None or n_chunks in chunks, n_chunks
     okv.prefill(toks)
     ln, pd, err = kv.state()
     assert ln[0] == prompt_len - 1 and pd[0] == toks[-1] and err == 0
@@ -131,12 +136,16 @@ def test_gamma_zero_and_long_prefill_chunks(S):
     _run_case(S, MID_GQA128, 300, 0, seed=3, n_rounds=2)
 
 
-@pytest.mark.parametrize("shape,prompt_len", [(MID_GQA128, 400), (MID_BF16, 101), (W.TINY, 200)],
-                         ids=["hd128-chunks-256+143", "hd64-qknorm-chunk-100", "tiny-f32-chunk-199"])
-def test_many_row_prefill_chunks(S, shape, prompt_len):
-    """Prefill chunks of more than 64 rows (workspace for 256) run the 128-row-tile GEMM: full and ragged
-    tiles, one and two tiles per chunk; the cache it writes must give the oracle's verify logits."""
-    _run_case(S, shape, prompt_len, 16, seed=4, n_rounds=2, ws_rows=256)
+@pytest.mark.parametrize("shape,prompt_len,chunks",
+                         [(MID_GQA128, 400, [1]), (MID_GQA128, 4400, range(2, 5)), (MID_GQA128, 300, [2]), (MID_BF16, 101, [1]),
+                          (W.TINY, 200, [1])],
+                         ids=["hd128-chunk-399", "hd128-chunks-over-1000", "hd128-chunks-256+43", "hd64-qknorm-chunk-100",
+                              "tiny-f32-chunk-199"])
+def test_many_row_prefill_chunks(S, shape, prompt_len, chunks):
+    """Prefill chunks of more than 64 rows (workspace for 256): one whole and ragged in tiles, several of them (4399 rows
+    are more than one chunk takes; the attention of the later ones reaches back over the first), and one with a short last chunk on the kernels for up to 64 rows; the
+    cache they write must give the oracle's verify logits."""
+    _run_case(S, shape, prompt_len, 16, seed=4, n_rounds=2, ws_rows=256, chunks=chunks)
 
 
 def test_tiny_config_full_pipeline(S):

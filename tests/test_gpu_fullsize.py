@@ -72,9 +72,9 @@ def test_one_layer_full_width_vs_oracle(S, shape):
 
 @pytest.mark.parametrize("P", [300, 150], ids=["chunks-256+43", "chunk-149"])
 def test_one_layer_full_width_long_prefill_vs_oracle(S, P):
-    """Prefill chunks of 256 and 149 rows at the full 32B width (workspace for 256-row chunks): every GEMM
-    runs all its 64-row tiles in one launch (4 full tiles; 2 full tiles and a ragged one); the verify logits
-    on the cache they wrote must match the oracle's."""
+    """Prefill chunks of 256 and 43, and of 149 rows at the full 32B width (workspace for 256 rows): the many-row GEMM on
+    whole and ragged row tiles, the short last chunk on the kernels for up to 64 rows; the verify logits on the cache
+    they wrote must match the oracle's."""
     shape = W.QWEN32B.with_layers(1)
     print(f"full-width 1-layer long prefill P={P}", flush=True)
     m = S.Model(shape)
@@ -83,7 +83,10 @@ def test_one_layer_full_width_long_prefill_vs_oracle(S, P):
     kv = S.KVCache(m, 1, P + gamma + 8)
     ws = m.workspace(256)
     toks = W.prompt(35, P, shape.vocab)
+    S.profile_start(1, 64)  # one embedding launch per chunk
     kv.prefill(0, to_dev_i32(toks), ws)
+    assert S.profile_read(1)[0] == (2 if P == 300 else 1)
+    S.profile_stop()
     om = _oracle_model(shape)
     okv = oracle.KV(om, P + gamma + 8)
     okv.prefill(toks)
