@@ -275,10 +275,10 @@ def test_batched_verify_over_64_rows(S, n):
 
 
 def test_batched_verify_full_width(S):
-    """Three sequences (99 rows) through one full-width Qwen3-32B layer and the real LM head: gate/up and the
-    LM head run the column-group-pair kernel at their real sizes (400 groups, one pair per workgroup; 1187
-    groups, an odd count, so the last pair holds one group, stream-K over the workgroup budget), qkv, o_proj
-    and down the many-row kernel on their stored split plans."""
+    """Three sequences (99 rows) through one full-width Qwen3-32B layer and the real LM head: the
+    many-row kernel at its real sizes: gate/up (400 groups, 200 pairs of one segment) and the LM head (1187 groups, an
+    odd count, so the last pair holds one group; one or two segments) a workgroup per tile, qkv, o_proj and down with
+    their 3, 3 and 6 segments shared out."""
     lens = W.rng(97).integers(16, 48, size=3)
     _batched(S, W.QWEN32B.with_layers(1), lens, 32, seed=98)
 

@@ -1,13 +1,14 @@
-"""The prefill attention kernel (chunks of more than 65 rows) against the block kernel.
+"""The prefill attention kernel (chunks of more than 64 rows) against the block kernel.
 
 A prompt prefilled in one or two large chunks runs the prefill kernel; the same prompt through a 16-row workspace runs in
-chunks of at most 64 rows on the block kernel, whose parity with the oracle is tested elsewhere.  The next block's
-logits read every cached K/V row.  Prompt lengths sit at and around the edges of the 128-query workgroups, 32-query
-waves and 32-position steps; head counts cover every spread of KV heads over the XCDs (8, 4, 3 and 40 KV heads) and
-query groups of 8, 7, 16 and 1 (blocks that split a row's heads).
+chunks of at most 16 rows on the block kernel, whose parity with the oracle is tested elsewhere.  The next block's
+logits read every cached K/V row.  Prompt lengths sit at and around the edges of the 48-query workgroups, 16-query
+tiles, 32-position steps and the steps' rounds over the 8 waves; head counts cover every spread of KV heads over the XCDs
+(8, 4, 3 and 40 KV heads) and query groups of 8, 7, 16 and 1 (tiles that split a row's heads).
 
-Bar: both sides are BF16 forwards of one model that differ in the order of their fp32 sums, so each logit row is within
-the BF16 parity bar of the other: max |z - z'| <= 2e-2 max |z'|.
+Bar: both sides are BF16 forwards of one model that differ in the order of their GEMMs' fp32 sums, so each logit row is
+within the BF16 parity bar of the other: max |z - z'| <= 2e-2 max |z'|.  (test_gpu_batch_bits.py compares the two kernels
+behind the same GEMMs, bit for bit.)
 """
 import pytest
 import torch

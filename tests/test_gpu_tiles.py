@@ -77,8 +77,8 @@ def test_batched_equals_single_full_width(S):
 
 @pytest.mark.parametrize("rows", [16, 64, 256, 2048])
 def test_prefill_chunks(S, rows):
-    """A prompt prefilled through workspaces of every size gives the same next block (one chunk, several equal
-    chunks, chunks of at most 64 rows)."""
+    """A prompt prefilled through workspaces of every size gives the same next block (one chunk or several,
+    chunks of at most 64 rows)."""
     m = S.Model(HD128)
     m.init_random(5, W.WEIGHT_SIGMA)
     n, R = 1333, 9
@@ -99,8 +99,8 @@ def test_prefill_chunks(S, rows):
 
 @pytest.mark.parametrize("n,R", [(3, 33), (5, 33), (16, 64)])
 def test_whole_rounds_then_split(S, n, R):
-    """A vocabulary of 9496 16-column tiles: the LM head's column blocks fill every compute unit twice or more unsplit (2, 3
-    and 4 row tiles per wave), and those left over (the last one only half inside the matrix) follow split over K."""
+    """A vocabulary of 9496 16-column tiles: the LM head's column blocks (the last one only half inside the matrix) fill every
+    compute unit twice or more, with 2, 3 and 4 row tiles per wave, and about half of them hold a segment's end."""
     shape = W.ModelShape(1, 4096, 4, 2, 128, 1024, 151936, 1e-6, 1e6, False, "bf16")
     m = S.Model(shape)
     m.init_random(7, W.WEIGHT_SIGMA)
@@ -108,8 +108,8 @@ def test_whole_rounds_then_split(S, n, R):
 
 
 def test_whole_rounds_then_split_prefill(S):
-    """A 3000-row chunk at the Qwen3-32B width (qkv, o_proj and down_proj fill the chip once and leave column blocks over)
-    gives the next block that 1000-row chunks give."""
+    """A 3000-row chunk at the Qwen3-32B width (a workgroup per tile, walking its segments) gives the next block that passes of
+    64 rows give."""
     shape = W.QWEN32B.with_layers(2)
     m = S.Model(shape)
     m.init_random(8, W.WEIGHT_SIGMA)
