@@ -154,7 +154,9 @@ int sdd_kv_state(sdd_kv* kv, int32_t* len, int32_t* pending, int32_t* error_bits
  * block on the device without a host round trip.  Read-only for callers. */
 int sdd_kv_device_state(sdd_kv* kv, const int32_t** len, const int32_t** pending);
 
-/* Workspace for prefill/verify of up to max_rows rows per call. */
+/* Workspace for prefill/verify of up to max_rows rows per call.  For more than
+ * 64 rows (bf16) it includes room for partial sums (640 KiB per compute unit),
+ * which prefills also take for longer chunks. */
 int sdd_workspace_bytes(const sdd_model* m, int max_rows, size_t* bytes);
 /* Prepares a caller-owned device workspace (zeroes its counters with a
  * kernel); needed once after allocation.  Every call leaves the counters zero

@@ -1229,8 +1229,10 @@ static size_t counters_bytes(const sdd_model* m) {
   return align_up((size_t)gemm_counter_count(m) * 4 * kCntStride, 256);
 }
 
-// Room for one workgroup's partial tile of a split many-row GEMM (320 rows x 256 columns fp32), twice: a launch may
-// hold two rounds of them.
+// Room for the many-row GEMM's partial and running sums, per compute unit.  A split launch needs one round of tiles
+// (320 rows x 256 columns fp32) times its partials per tile; the LM head's running sums, one per segment boundary, one
+// round per 320 rows of the call.  Twice a round keeps both whole at the named widths up to 640 rows (with less the planner
+// takes smaller tiles or more launches); a prefill takes its longer chunks' rows from the same room.
 constexpr size_t kTilePartBytes = (size_t)2 * 320 * 256 * 4;
 constexpr int kPrefillMaxRows = 4096;  // rows per prefill chunk at most
 
