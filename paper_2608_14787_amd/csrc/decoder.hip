@@ -1270,7 +1270,7 @@ static size_t part_min_bytes(const WsLayout& L) { return (size_t)L.n_wg * 2 * kM
 WsLayout ws_layout(const sdd_model* m, int max_rows) {
   WsLayout L = rows_layout(m, max_rows);
   L.part_bytes = part_min_bytes(L);
-  // the many-row kernel (bf16, more than 64 rows) gets room for every workgroup's tile of a split launch
+  // the many-row kernel (bf16, more than 64 rows) adds up partial and running sums
   if (m->es == 2 && max_rows > kMaxPassRows) L.part_bytes = std::max(L.part_bytes, (size_t)L.n_wg * kTilePartBytes);
   L.part = L.total;
   L.amax = align_up(L.part + L.part_bytes, 256);
