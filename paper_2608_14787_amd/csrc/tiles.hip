@@ -643,7 +643,6 @@ __global__ void __launch_bounds__(kTileThreads, 1) gemm_tile_kernel(GemmArgs a) 
         }
     });
   } else {
-
   // Split item: every contributor stores its segments' sums (16-byte device-coherent stores) and the item is finished in E
   // shares of (row tile, wave column) units, each summed in segment order.  A contributor waits for the others for a
   // bounded time (a split launch has at most one workgroup per compute unit, so all of them are normally running; where
@@ -816,6 +815,8 @@ TilePlan plan_tiles(const MatPlan& mp, bool pairs, int M, int n_cu, size_t part_
 }
 
 int launch_gemm_tiles(const TilePlan& p, int epi, GemmArgs a, hipStream_t st) {
+  if (p.per < 1)  // (room for the running sums of 128 columns always plans)
+    return fail(SDD_EUNSUPPORTED, "many-row GEMM: no plan for %d rows in this workspace", a.M);
   for (int cb0 = 0; cb0 < p.ncb; cb0 += p.per) {
     tile_launch(a, p, cb0);
     switch (epi) {
